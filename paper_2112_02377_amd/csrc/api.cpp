@@ -76,7 +76,7 @@ Handle::~Handle()
 // Compute units and LDS bytes per workgroup of the current device (queried
 // once; the initialisation of a function-local static is thread-safe, and
 // retried if it throws).
-static int num_cus()
+int num_cus()
 {
     static const int cus = [] {
         int dev = 0, n = 0;
@@ -124,6 +124,7 @@ void Handle::replan(int mode, int32_t nparts, const int32_t* sub_grid)
         prm.lds_elems = (int32_t)std::min<int64_t>(opt.lds_elems, cap);
     }
     prm.staged = (mode != JAC_BANDROW);
+    prm.fill_gap = mode == JAC_BANDROW_SP ? 2 : 0;
     prm.tables = opt.tables != 0;
     Plan pl = make_plan(pa, np.cuts, prm);
     // caller entry -> slot
@@ -171,6 +172,13 @@ void Handle::replan(int mode, int32_t nparts, const int32_t* sub_grid)
         d.tile_fp.reset(); d.tile_own.reset();
     }
     upload(d.shift, plan.shift, stream);
+    if (!plan.res_run0.empty()) {
+        std::vector<int32_t> all;
+        for (const std::vector<int32_t>* v : {&plan.res_run0, &plan.res_run_lds, &plan.res_run_delta, &plan.res_fp,
+                                              &plan.res_own, &plan.res_shift})
+            all.insert(all.end(), v->begin(), v->end());
+        upload(d.res_plan, all, stream);
+    }
     upload(d.slot_of_caller, slot_of_caller, stream);
     upload(d.diag_slot, diag32, stream);
     upload(d.perm, part.perm, stream);
@@ -732,6 +740,9 @@ jac_status jac_sweep(jac_handle h, int32_t nsweeps, double* hist_dev)
         if (nsweeps == 0) return JAC_OK;
         ++h->state_gen;
         std::vector<SysDev> sys = {h->sysdev(false)};
+        SysState st;
+        if (run_resident(*h, sys[0], false, false, nsweeps, 0, hist_dev, h->d.x0.p, h->d.x1.p, h->d.x0.p, st))
+            return JAC_OK;
         std::vector<int32_t> tb = {0, h->plan.ntiles};
         run_loop(*h, sys, false, false, nsweeps, 0, hist_dev, h->d.sys, h->d.state, h->d.tile_base, tb,
                  h->lds_fp_bytes(false), h->lds_tab(), h->plan.colfmt, h->nrhs);
@@ -753,13 +764,18 @@ static jac_status solve64(Handle& h, double tol, int32_t maxit, int norm, int32_
         s.thr[c] = tol * scale[c];
         s.big[c] = 1e150 * std::max(bn, 1.0);
     }
-    std::vector<SysDev> sys = {s};
-    std::vector<int32_t> tb = {0, h.plan.ntiles};
-    run_loop(h, sys, false, true, maxit, norm == JAC_NORM_INF_ABS ? 1 : 0, nullptr, h.d.sys, h.d.state,
-             h.d.tile_base, tb, h.lds_fp_bytes(false), h.lds_tab(), h.plan.colfmt, h.nrhs);
     SysState st;
-    JAC_HIP(hipMemcpyAsync(&st, h.d.state.p, sizeof(SysState), hipMemcpyDeviceToHost, h.stream));
-    h.sync();
+    const int norm_inf = norm == JAC_NORM_INF_ABS ? 1 : 0;
+    const bool resident =
+        run_resident(h, s, false, true, maxit, norm_inf, nullptr, h.d.x0.p, h.d.x1.p, h.d.x0.p, st);
+    if (!resident) {
+        std::vector<SysDev> sys = {s};
+        std::vector<int32_t> tb = {0, h.plan.ntiles};
+        run_loop(h, sys, false, true, maxit, norm_inf, nullptr, h.d.sys, h.d.state, h.d.tile_base, tb,
+                 h.lds_fp_bytes(false), h.lds_tab(), h.plan.colfmt, h.nrhs);
+        JAC_HIP(hipMemcpyAsync(&st, h.d.state.p, sizeof(SysState), hipMemcpyDeviceToHost, h.stream));
+        h.sync();
+    }
     uint32_t which = 0;
     h.last_loop_sweeps = st.last_k + 1;
     for (int c = 0; c < h.nrhs; ++c) {
@@ -767,7 +783,7 @@ static jac_status solve64(Handle& h, double tol, int32_t maxit, int norm, int32_
         if (sweeps_out) sweeps_out[c] = st.stop_k[c];
         if (relres_out) relres_out[c] = st.nrm[c] / scale[c];
     }
-    h.settle(which);
+    if (!resident) h.settle(which);
     h.last_status = st.status;
     if (st.status == JAC_E_DIVERGED) fail(JAC_E_DIVERGED, "residual norm diverged");
     return (jac_status)st.status;

@@ -70,6 +70,10 @@ struct DeviceArrays {
     // working buffers, kept between calls (grow-only)
     DevMem t_map, a_gcol;
     DevMem adj_ck, adj_X, adj_M, adj_lam0, adj_lam1, adj_carry, adj_gb, adj_G, adj_sys, adj_segs, adj_fsegs;
+    // resident loop: LDS layout of unstaged shift tables (the plan's res_
+    // arrays one after another), and one buffer for the ring of iterates,
+    // norm partials, descriptor and control words
+    DevMem res_plan, res_work;
     // asynchronous solve: descriptor, residual scratch, norms
     DevMem async_sys, async_r32, async_norm;
 };
@@ -82,6 +86,9 @@ struct Handle {
     int32_t grid[3] = {0, 0, 0};
     bool has_grid = false;
     bool planned = false;
+    uint32_t res_next = 0;         // resident launches: number of the next launch's first sweep
+    uint32_t res_arrived = 0;      // workgroups they have started
+    bool res_off = false;          // a resident launch gave up: per-sweep launches from then on
     Partition part;
     Plan plan;
     Options opt;
@@ -129,11 +136,20 @@ struct Handle {
     int lds_tab() const;
 };
 
+int num_cus();
 int loop_grid(void* fn, int block, size_t lds, int wg_per_cu, int64_t work);
 int sweep_grid(const Handle& h, void* fn, int block, size_t lds);
 void run_loop(Handle& h, std::vector<SysDev>& sys, bool fp32, bool solve, int32_t kend, int norm_inf, double* hist,
               DevMem& d_sys, DevMem& d_state, DevMem& d_tile_base, const std::vector<int32_t>& tile_base,
               int fp_bytes, int runs, int colfmt, int nrhs, const std::vector<int64_t>* sys_bytes = nullptr);
+// The loop of one system in one resident launch (resident.cpp).  False, with
+// the starting iterate intact, when the split does not fit the chip, the
+// loop is too short or an option asks for per-sweep launches, or when the
+// launch gave up; the caller then runs run_loop.  Else the iterate is in
+// xout -- copied to x0_out when given -- and st holds the stop sweeps and
+// norms (solve mode).
+bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t kend, int norm_inf, double* hist,
+                  const void* x0, void* xout, void* x0_out, SysState& st);
 jac_status solve_refine(Handle& h, double tol, int32_t maxit, int norm, int32_t* sweeps_out, double* relres_out);
 void set_last_error(const std::string& m);
 

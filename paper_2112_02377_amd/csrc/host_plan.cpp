@@ -40,6 +40,19 @@ void footprint(const Csr& a, int32_t r0, int32_t r1, Footprint& fp)
         if (m == 0 || fp.cols[m] != fp.cols[m - 1] + 1) ++fp.runs;
 }
 
+// Adds the columns of holes of at most `gap` columns between referenced ones.
+void fill_holes(Footprint& f, int32_t gap)
+{
+    const size_t m0 = f.cols.size();
+    for (size_t m = 1; m < m0; ++m)
+        if (f.cols[m] - f.cols[m - 1] <= gap + 1)
+            for (int32_t c = f.cols[m - 1] + 1; c < f.cols[m]; ++c) {
+                f.cols.push_back(c);
+                if (c + 1 == f.cols[m]) --f.runs;
+            }
+    std::inplace_merge(f.cols.begin(), f.cols.begin() + (std::ptrdiff_t)m0, f.cols.end());
+}
+
 }  // namespace
 
 Plan make_plan(const Csr& a, const std::vector<int32_t>& cuts_in, const PlanParams& prm_in)
@@ -95,41 +108,104 @@ Plan make_plan(const Csr& a, const std::vector<int32_t>& cuts_in, const PlanPara
     }
     pl.colfmt = prm.staged ? COL_LOCAL16 : (rel16 ? COL_REL16 : COL_GLOBAL32);
     const int64_t col_bytes = pl.colfmt == COL_GLOBAL32 ? 4 : 2;
-    // the shift of entry (i, c): c - i, or its LDS position in tile t minus i
-    auto shift_of = [&](int32_t t, int32_t i, int32_t c) -> int32_t {
-        if (!prm.staged) return c - i;
-        const std::vector<int32_t>& cols = fps[t].cols;
-        return (int32_t)(std::lower_bound(cols.begin(), cols.end(), c) - cols.begin()) - i;
-    };
     pl.tile_slice0.assign((size_t)pl.ntiles + 1, 0);
     pl.slice_row0.clear();
     pl.slice_width.clear();
     pl.slice_off.assign(1, 0);
-    pl.shift.clear();
+    // Staged: LDS position of every entry.  A row's k-th column is most often
+    // one past the previous row's k-th, else it is searched.
+    std::vector<int32_t> lpos;
+    auto positions = [&]() {
+        lpos.resize(a.ci.size());
+        for (int32_t t = 0; t < pl.ntiles; ++t) {
+            const std::vector<int32_t>& cols = fps[t].cols;
+            const int32_t m = (int32_t)cols.size();
+            for (int32_t i = pl.tile_row0[t]; i < pl.tile_row0[t + 1]; ++i) {
+                const bool prev = i > pl.tile_row0[t];
+                for (int32_t p = a.rp[i]; p < a.rp[i + 1]; ++p) {
+                    const int32_t up = prev && p - a.rp[i] < a.rp[i] - a.rp[i - 1] ? lpos[a.rp[i - 1] + (p - a.rp[i])] + 1 : m;
+                    lpos[p] = up < m && cols[up] == a.ci[p]
+                                  ? up
+                                  : (int32_t)(std::lower_bound(cols.begin(), cols.end(), a.ci[p]) - cols.begin());
+                }
+            }
+        }
+    };
+    // the shift of entry p of row i: column minus i, or its LDS position minus i
+    auto shift_of = [&](int32_t i, int32_t p) { return (prm.staged ? lpos[p] : a.ci[p]) - i; };
     std::vector<int32_t> w_ell, w_tab;          // per slice
     std::vector<int32_t> keys;
     int64_t ell_bytes = 0, tab_bytes = 0;
-    for (int32_t t = 0; t < pl.ntiles; ++t) {
-        pl.tile_slice0[t] = (int32_t)pl.slice_row0.size();
-        for (int32_t r = pl.tile_row0[t]; r < pl.tile_row0[t + 1]; r += kSlice) {
-            const int32_t re = std::min(pl.tile_row0[t + 1], r + kSlice);
-            int32_t w = 0;
-            for (int32_t i = r; i < re; ++i) w = std::max(w, a.rp[i + 1] - a.rp[i]);
-            int32_t wt = 0;
-            if (prm.tables) {
-                keys.clear();
-                for (int32_t i = r; i < re; ++i)
-                    for (int32_t p = a.rp[i]; p < a.rp[i + 1]; ++p) keys.push_back(shift_of(t, i, a.ci[p]));
-                std::sort(keys.begin(), keys.end());
-                keys.erase(std::unique(keys.begin(), keys.end()), keys.end());
-                wt = (int32_t)keys.size();
-                pl.shift.insert(pl.shift.end(), keys.begin(), keys.end());
+    int32_t max_tab_width = 0;
+    auto slices = [&]() {
+        pl.slice_row0.clear();
+        pl.shift.clear();
+        w_ell.clear();
+        w_tab.clear();
+        ell_bytes = tab_bytes = 0;
+        max_tab_width = 0;
+        if (prm.staged) positions();
+        for (int32_t t = 0; t < pl.ntiles; ++t) {
+            pl.tile_slice0[t] = (int32_t)pl.slice_row0.size();
+            for (int32_t r = pl.tile_row0[t]; r < pl.tile_row0[t + 1]; r += kSlice) {
+                const int32_t re = std::min(pl.tile_row0[t + 1], r + kSlice);
+                int32_t w = 0;
+                for (int32_t i = r; i < re; ++i) w = std::max(w, a.rp[i + 1] - a.rp[i]);
+                int32_t wt = 0;
+                if (prm.tables) {
+                    // the distinct shifts, ascending: the rows of a stencil
+                    // have the same few, so a small sorted list is searched
+                    // from the last hit on; many distinct ones are sorted
+                    keys.clear();
+                    bool sorted = true;
+                    for (int32_t i = r; i < re; ++i) {
+                        size_t at = 0;
+                        for (int32_t p = a.rp[i]; p < a.rp[i + 1]; ++p) {
+                            const int32_t key = shift_of(i, p);
+                            if (!sorted) {
+                                keys.push_back(key);
+                                continue;
+                            }
+                            while (at < keys.size() && keys[at] < key) ++at;
+                            if (at == keys.size() || keys[at] != key) keys.insert(keys.begin() + (std::ptrdiff_t)at, key);
+                            sorted = keys.size() < 128;
+                        }
+                    }
+                    if (!sorted) {
+                        std::sort(keys.begin(), keys.end());
+                        keys.erase(std::unique(keys.begin(), keys.end()), keys.end());
+                    }
+                    wt = (int32_t)keys.size();
+                    max_tab_width = std::max(max_tab_width, wt);
+                    pl.shift.insert(pl.shift.end(), keys.begin(), keys.end());
+                }
+                pl.slice_row0.push_back(r);
+                w_ell.push_back(w);
+                w_tab.push_back(wt);
+                ell_bytes += (int64_t)w * kSlice * (8 + col_bytes);
+                tab_bytes += (int64_t)wt * kSlice * 8;
             }
-            pl.slice_row0.push_back(r);
-            w_ell.push_back(w);
-            w_tab.push_back(wt);
-            ell_bytes += (int64_t)w * kSlice * (8 + col_bytes);
-            tab_bytes += (int64_t)wt * kSlice * 8;
+        }
+    };
+    slices();
+    // A staged table whose widest slices the resident loop cannot hold: stage
+    // the holes of the footprints too, if that narrows them enough.  A hole
+    // shifts the LDS positions behind it, so that a slice reaches its columns
+    // through more shifts, each a padded slot for all its rows (80^3 27-point
+    // matrix with a tenth of its edges dropped: 30 slots in the widest slices,
+    // 27 with holes of up to two columns staged).
+    if (prm.staged && prm.tables && tab_bytes < ell_bytes && max_tab_width > kResWidth &&
+        max_tab_width <= kResWidth + 13 && prm.fill_gap > 0) {
+        const std::vector<Footprint> plain = fps;
+        bool fits = true;
+        for (Footprint& f : fps) {
+            fill_holes(f, prm.fill_gap);
+            fits = fits && (int32_t)f.cols.size() <= prm.lds_elems;
+        }
+        if (fits) slices();
+        if (!fits || max_tab_width > kResWidth) {
+            fps = plain;
+            slices();
         }
     }
     // one format for the whole plan: the kernels then carry no per-slice choice
@@ -215,7 +291,7 @@ Plan make_plan(const Csr& a, const std::vector<int32_t>& cuts_in, const PlanPara
                 const int32_t* sh = pl.shift.data() + off / kSlice;
                 for (int32_t i = row0; i < std::min(r1, row0 + kSlice); ++i)
                     for (int32_t p = a.rp[i]; p < a.rp[i + 1]; ++p) {
-                        const int32_t key = shift_of(t, i, a.ci[p]);
+                        const int32_t key = shift_of(i, p);
                         const int32_t k = (int32_t)(std::lower_bound(sh, sh + w, key) - sh);
                         const int64_t slot = off + (int64_t)k * kSlice + (i - row0);
                         pl.slot_of_nnz[p] = slot;
@@ -239,9 +315,7 @@ Plan make_plan(const Csr& a, const std::vector<int32_t>& cuts_in, const PlanPara
                         pl.slot_of_nnz[p] = slot;
                         if (c == i) pl.diag_slot[i] = slot;
                         if (prm.staged) {
-                            const int32_t loc =
-                                (int32_t)(std::lower_bound(cols->begin(), cols->end(), c) - cols->begin());
-                            pl.col16[slot] = (uint16_t)loc;
+                            pl.col16[slot] = (uint16_t)lpos[p];
                         } else if (rel16) {
                             pl.col16[slot] = (uint16_t)(int16_t)(c - i);
                         } else {
@@ -295,6 +369,59 @@ Plan make_plan(const Csr& a, const std::vector<int32_t>& cuts_in, const PlanPara
         }
         pl.xcd_tile0[0] = 0;
         pl.xcd_tile0[8] = pl.ntiles;
+    }
+    for (int32_t s = 0; s < pl.nslices; ++s) pl.max_width = std::max(pl.max_width, pl.slice_width[s]);
+    for (int32_t t = 0; t < pl.ntiles; ++t)
+        pl.max_tile_slices = std::max(pl.max_tile_slices, pl.tile_slice0[t + 1] - pl.tile_slice0[t]);
+    if (prm.staged) {
+        pl.res_max_fp = pl.max_fp;
+        pl.res_max_runs = pl.max_runs;
+        for (int32_t t = 0; t < pl.ntiles; ++t)
+            pl.res_max_halo = std::max(pl.res_max_halo, pl.tile_fp[t] - (pl.tile_row0[t + 1] - pl.tile_row0[t]));
+    } else if (tables && pl.max_width <= kResWidth) {
+        // per tile, the union of the intervals row + shift of its slices
+        pl.res_run0.assign(1, 0);
+        pl.res_shift.assign(pl.shift.size(), 0);
+        std::vector<std::pair<int32_t, int32_t>> iv;       // [first, end) columns
+        for (int32_t t = 0; t < pl.ntiles; ++t) {
+            const int32_t r1 = pl.tile_row0[t + 1];
+            iv.clear();
+            for (int32_t s = pl.tile_slice0[t]; s < pl.tile_slice0[t + 1]; ++s) {
+                const int32_t row0 = pl.slice_row0[s], re = std::min(r1, row0 + kSlice);
+                for (int64_t k = pl.slice_off[s] / kSlice; k < pl.slice_off[s + 1] / kSlice; ++k)
+                    iv.emplace_back(std::max(row0 + pl.shift[k], 0), std::min(re + pl.shift[k], n));
+            }
+            std::sort(iv.begin(), iv.end());
+            const size_t first_run = pl.res_run_lds.size();
+            int32_t fpn = 0, end = -1;
+            for (const auto& v : iv) {
+                if (end < 0 || v.first > end) {
+                    pl.res_run_lds.push_back(fpn);
+                    pl.res_run_delta.push_back(v.first - fpn);
+                    fpn += v.second - v.first;
+                    end = v.second;
+                } else if (v.second > end) {
+                    fpn += v.second - end;
+                    end = v.second;
+                }
+            }
+            // run holding column c: the last whose first column is at or below c
+            auto delta_of = [&](int32_t c) {
+                size_t q = first_run;
+                while (q + 1 < pl.res_run_lds.size() && pl.res_run_lds[q + 1] + pl.res_run_delta[q + 1] <= c) ++q;
+                return pl.res_run_delta[q];
+            };
+            for (int32_t s = pl.tile_slice0[t]; s < pl.tile_slice0[t + 1]; ++s)
+                for (int64_t k = pl.slice_off[s] / kSlice; k < pl.slice_off[s + 1] / kSlice; ++k)
+                    pl.res_shift[k] = pl.shift[k] - delta_of(std::max(pl.slice_row0[s] + pl.shift[k], 0));
+            const int32_t r0 = pl.tile_row0[t], nr = (int32_t)(pl.res_run_lds.size() - first_run);
+            pl.res_run0.push_back((int32_t)pl.res_run_lds.size());
+            pl.res_fp.push_back(fpn);
+            pl.res_own.push_back(r0 - delta_of(r0));
+            pl.res_max_fp = std::max(pl.res_max_fp, fpn);
+            pl.res_max_halo = std::max(pl.res_max_halo, fpn - (r1 - r0));
+            pl.res_max_runs = std::max(pl.res_max_runs, nr);
+        }
     }
     // a batch of slots may read up to 7 shifts past the last slice's last one
     if (tables) pl.shift.insert(pl.shift.end(), kSlice, 0);

@@ -66,6 +66,7 @@ struct PlanParams {
     int32_t tile_rows = 1024;       // multiple of kSlice
     int32_t lds_elems = 4096;       // max staged x entries per tile
     int32_t max_runs = 1024;        // max footprint runs per tile
+    int32_t fill_gap = 0;           // staged tables: holes of at most this many columns may be staged too
     bool staged = false;            // stage x through LDS with 16-bit local columns
     bool rel16 = true;              // unstaged: 16-bit row-relative columns when every |j - i| fits
     bool tables = true;             // per-slice tables of column shifts where they stream fewer bytes
@@ -82,6 +83,9 @@ enum ColFormat { COL_GLOBAL32 = 0, COL_REL16 = 1, COL_LOCAL16 = 2, COL_TABG = 3,
 // against run starts held in registers; a tile with more uses its chunk
 // table of run-start bits.
 constexpr int32_t kRegRuns = 4;
+
+// Slots per row the resident loop can hold in registers (resident.hip).
+constexpr int32_t kResWidth = 27;
 
 struct Plan {
     PlanParams prm;
@@ -133,6 +137,15 @@ struct Plan {
     // zero (the kernel clamps the column into range); 64 trailing zeros
     std::vector<int32_t> shift;
     int64_t table_slots = 0;          // slots when the plan uses a shift table
+    // Footprints for the resident loop (resident.hip), which keeps x in LDS
+    // whatever the split.  Staged plans: the arrays above.  Unstaged shift
+    // tables: the columns a tile's tables reach (a superset of the stored
+    // ones), as runs, and the table with LDS positions; empty when a plan
+    // has neither (explicit unstaged columns).
+    std::vector<int32_t> res_run0, res_run_lds, res_run_delta, res_fp, res_own, res_shift;
+    int32_t max_width = 0;            // slots of the widest slice
+    int32_t max_tile_slices = 0;
+    int32_t res_max_fp = 0, res_max_halo = 0, res_max_runs = 0;   // entries staged, entries of other tiles, runs
 };
 
 Plan make_plan(const Csr& pa, const std::vector<int32_t>& cuts, const PlanParams& prm);

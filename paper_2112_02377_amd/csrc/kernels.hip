@@ -31,6 +31,7 @@
 #include <cmath>
 #include <cstdint>
 
+#include "device.h"
 #include "kernels.h"
 #include "launch.h"
 
@@ -41,109 +42,12 @@ namespace {
 constexpr int KB = 8;      // slot batch: loads issued together before use
 constexpr int SU = 8;      // staging batch
 
-// Pointer into global (device) memory: lets the compiler emit global_* loads.
-template <typename V>
-using gptr = __attribute__((address_space(1))) V*;
-// Pointer into memory no workgroup writes during the launch (the tile and
-// slice layout): wave-uniform reads through it become scalar loads.
-template <typename V>
-using cptr = __attribute__((address_space(4))) V*;
-
-// Coherent (device-wide) relaxed accesses for the few words workgroups of one
-// persistent launch exchange; no cache-wide maintenance is implied.
-__device__ __forceinline__ int32_t ld_dev(const int32_t* p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double ld_dev(const double* p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_dev(int32_t* p, int32_t v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_dev(double* p, double v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Plain or coherent access, chosen at compile time.
-template <bool DEV, typename V>
-__device__ __forceinline__ V ldv(const V* p)
-{
-    if constexpr (DEV) return ld_dev(p);
-    else return *p;
-}
-template <bool DEV, typename V>
-__device__ __forceinline__ void stv(V* p, V v)
-{
-    if constexpr (DEV) st_dev(p, v);
-    else *p = v;
-}
-
-__device__ __forceinline__ double maxnan(double a, double b)
-{
-    return (b > a || b != b) ? b : a;
-}
-
 template <typename T> struct Vec;
 template <> struct Vec<double> { static __device__ __forceinline__ double zero() { return 0.0; } };
 template <> struct Vec<float> { static __device__ __forceinline__ float zero() { return 0.0f; } };
 
 __device__ __forceinline__ double fmaT(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float fmaT(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-
-// Reduce NRHS values over the workgroup in a fixed order; result in thread 0.
-template <int NRHS>
-__device__ __forceinline__ void block_reduce(double (&v)[NRHS], bool is_max, double* red)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-#pragma unroll
-        for (int c = 0; c < NRHS; ++c) {
-            const double o = __shfl_xor(v[c], off, 64);
-            v[c] = is_max ? maxnan(v[c], o) : v[c] + o;
-        }
-    }
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-    if (lane == 0) {
-#pragma unroll
-        for (int c = 0; c < NRHS; ++c) red[wave * NRHS + c] = v[c];
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int c = 0; c < NRHS; ++c) {
-            double a = red[c];
-            for (int w = 1; w < nw; ++w) a = is_max ? maxnan(a, red[w * NRHS + c]) : a + red[w * NRHS + c];
-            v[c] = a;
-        }
-    }
-    __syncthreads();
-}
-
-// Items [0,T) shared by G workgroups, XCD-aware.  Workgroup ids are dealt to
-// the 8 XCDs round-robin, so XCD x holds workgroups x, x+8, ...; each XCD gets
-// one contiguous block of items (sizes differing by at most one, the same
-// split as its workgroup count when G == T, so then every workgroup gets
-// exactly one item) and neighbouring tiles, which share x halos, meet in the
-// same L2.
-__device__ __forceinline__ void xcd_items(int32_t T, int32_t G, int32_t wg, int32_t& first, int32_t& end,
-                                          int32_t& stride)
-{
-    if (G < 8) {
-        first = wg; end = T; stride = G;
-        return;
-    }
-    const int32_t x = wg & 7, l = wg >> 3;
-    const int32_t gx = (G - x + 7) >> 3;                  // workgroups on this XCD
-    const int32_t q = T >> 3, r = T & 7;
-    const int32_t s0 = x * q + min(x, r);
-    first = s0 + l;
-    end = s0 + q + (x < r ? 1 : 0);
-    stride = gx;
-}
 
 // ---------------------------------------------------------------------------
 // One tile of one sweep: stage the footprint (staged tiles), then one slice

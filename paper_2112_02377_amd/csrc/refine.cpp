@@ -97,7 +97,6 @@ jac_status solve_refine(Handle& h, double tol, int32_t maxit, int norm, int32_t*
         if (done == full || status == JAC_E_DIVERGED) break;
 
         // inner FP32 solve on A d = r32 from d = 0
-        JAC_HIP(hipMemsetAsync(h.d.d0.p, 0, fbytes, h.stream));
         SysDev s32 = h.sysdev(true);
         s32.b = h.d.r32.p;
         s32.x[0] = h.d.d0.p;
@@ -115,21 +114,26 @@ jac_status solve_refine(Handle& h, double tol, int32_t maxit, int norm, int32_t*
             }
         }
         budget = std::max(budget, 1);
-        std::vector<SysDev> sys = {s32};
-        std::vector<int32_t> tb = {0, h.plan.ntiles};
-        run_loop(h, sys, true, true, budget, norm_inf, nullptr, h.d.sys, h.d.state, h.d.tile_base, tb, fpb32, tab,
-                 h.plan.colfmt, nr);
-        t_inner_ms += h.last_loop_ms;
         SysState st;
-        JAC_HIP(hipMemcpyAsync(&st, h.d.state.p, sizeof(SysState), hipMemcpyDeviceToHost, h.stream));
-        h.sync();
+        const bool resident =
+            run_resident(h, s32, true, true, budget, norm_inf, nullptr, nullptr, h.d.d0.p, nullptr, st);
+        if (!resident) {
+            JAC_HIP(hipMemsetAsync(h.d.d0.p, 0, fbytes, h.stream));
+            std::vector<SysDev> sys = {s32};
+            std::vector<int32_t> tb = {0, h.plan.ntiles};
+            run_loop(h, sys, true, true, budget, norm_inf, nullptr, h.d.sys, h.d.state, h.d.tile_base, tb, fpb32, tab,
+                     h.plan.colfmt, nr);
+            JAC_HIP(hipMemcpyAsync(&st, h.d.state.p, sizeof(SysState), hipMemcpyDeviceToHost, h.stream));
+            h.sync();
+        }
+        t_inner_ms += h.last_loop_ms;
         if (st.status == JAC_E_DIVERGED) {
             status = JAC_E_DIVERGED;
             break;
         }
         uint32_t which = 0;
         for (int c = 0; c < nr; ++c) {
-            which |= (uint32_t)(st.stop_k[c] % 3) << (2 * c);
+            if (!resident) which |= (uint32_t)(st.stop_k[c] % 3) << (2 * c);
             if (!((done >> c) & 1u)) {
                 inner_total[c] += st.stop_k[c];
                 // the inner residual starts at r (d = 0): its last norm over

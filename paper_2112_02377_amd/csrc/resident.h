@@ -1,0 +1,97 @@
+// Resident sweep loop: device structures and launchers (resident.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "kernels.h"
+
+namespace jac {
+
+constexpr int kResBlock = 256;      // threads per workgroup: the norm's summation order is that of 256-thread launches
+constexpr int kResRing = 8;         // iterates in flight: x_k lives in ring slot k mod 8
+constexpr int kResPart = 16;        // norm partials in flight, by sweep mod 16
+// Footprint entries of other tiles a thread gathers per sweep, at most: a
+// 512-row tile of a 7-point row's matrix has up to 1280 of them on planes of
+// 128 x 128 nodes, of a 27-point row's up to 1606 on 96 x 96.
+constexpr int res_halo(int width) { return width <= 7 ? 5 : 7; }
+constexpr int kResDeciders = 4;     // deciding workgroups of a single system (sweep k is decided by number k mod 4)
+
+constexpr int kResRed = 16;         // doubles of reduction scratch (deciding workgroups); 8 control words follow
+constexpr int kResGaveUp = 16;
+constexpr int kResCtlWords = 20 + 2 * kResRed;   // control words and scratch of a tile in LDS
+
+// Bytes of x in LDS: ldx entries per right-hand side.
+constexpr size_t res_x_bytes(size_t ldx, size_t nrhs, size_t elem) { return (ldx * nrhs * elem + 15) / 16 * 16; }
+
+// Two x buffers in LDS (one barrier per sweep instead of two) where that does
+// not cost a workgroup per CU.
+constexpr bool res_two_buffers(int nrhs, int width, bool loc) { return nrhs == 1 && !(loc && width > 14); }
+// Norm partials a tile stores per sweep and right-hand side: one per wave
+// where the tile has no barrier to add them behind.
+constexpr int res_partials(int nrhs, int width, bool loc) { return res_two_buffers(nrhs, width, loc) ? kResBlock / 64 : 1; }
+// b in LDS instead of registers: the FP64 27-point table kernel is four registers short without.
+constexpr bool res_rhs_in_lds(size_t elem, int nrhs, int width, bool loc)
+{
+    return elem == 8 && nrhs == 1 && width > 14 && !loc;
+}
+
+// Control words of one system, exchanged by its workgroups during a launch.
+// They are never reset: sweep k of a launch is written as kbase + k (modulo
+// 2^32), with a kbase beyond every sweep of the launches before, so what an
+// earlier launch left reads as "not yet".
+struct ResCtl {
+    uint32_t word[8];               // last sweep each deciding workgroup has decided
+    uint32_t stop[4];               // column stopped on the residual of this sweep
+    uint32_t done;                  // kbase of the launch: every column has stopped
+    uint32_t abort;                 // kbase of the launch: a wait ran out, every workgroup leaves
+    uint32_t arrived;               // workgroups that have cleared their share of the ring, all launches
+    int32_t status;                 // JAC_OK, JAC_NOT_CONVERGED, JAC_E_DIVERGED
+    int32_t last_k;                 // last sweep that stopped a column
+    int32_t pad_;
+    double nrm[4];                  // norm of the returned iterate per column
+};
+
+// One system of a resident launch (kernel argument).
+struct ResSys {
+    const int32_t* tile_row0;
+    const int32_t* tile_slice0;
+    const int64_t* slice_off;
+    const int32_t* run0;            // footprint runs per tile: first LDS position, global column minus LDS position
+    const int32_t* run_lds;
+    const int32_t* run_delta;
+    const int32_t* fp;              // footprint entries per tile
+    const int32_t* own;             // LDS position of the tile's first row
+    const int32_t* shift;           // shift-table splits: LDS position minus row, per slot column
+    const uint16_t* col16;          // explicit splits: LDS position per slot
+    const void* val;                // slot values, T
+    const void* b;                  // T, node-major [n][nrhs]
+    const void* x0;                 // starting iterate, T (null: zero)
+    void* xout;                     // returned iterate, T
+    void* ring;                     // T [kResRing][nrhs][n]: iterates as their tiles publish them
+    double* part;                   // [kResPart][ntiles][res_partials][nrhs]
+    ResCtl* ctl;
+    int32_t n, ntiles;
+    double thr[4];
+    double big[4];
+};
+
+struct ResParams {
+    ResSys sys;
+    double* hist;                   // nullable, [k * nrhs + c]
+    uint32_t kbase;                 // see ResCtl
+    uint32_t arrive;                // ctl->arrived once every workgroup of this launch has arrived
+    int32_t nd;                     // deciding workgroups (1, 2, 4 or 8)
+    int32_t kend, solve, norm_inf;
+};
+
+// Kernel for slots per row (7, 14 or 28) and slices per wave (2 or 4), or null when there is none.
+void* res_kernel(bool fp32, int nrhs, int width, int slices, bool explicit_cols);
+// ldx: x entries in LDS per right-hand side; lds: see res_lds in resident.cpp
+void launch_res(void* fn, int grid, size_t lds, int32_t ldx, hipStream_t st, ResParams p);
+// x0 = xout unless the launch gave up
+void launch_res_settle(bool fp32, hipStream_t st, const void* xout, void* x0, int64_t m, const ResCtl* ctl,
+                       uint32_t kbase);
+
+}  // namespace jac

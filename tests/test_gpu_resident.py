@@ -1,0 +1,170 @@
+"""GPU: the resident sweep loop, which a split that fits the chip takes by
+default, against per-sweep launches (JAC_OPT_GRID = 1 asks for them) and the
+oracle.  Tiles, summation order and norms are the same, so every result is
+bit-identical; the oracle bound is the per-sweep rounding of the row sums
+(1e-12 relative per checked sweep, as for every other sweep path)."""
+import threading
+
+import numpy as np
+import pytest
+import scipy.sparse as sp
+
+from gpu_util import B, get_x, make, need_gpu, rel_inf, set_x, sweep, torch
+from oracle import ref
+from paper_2112_02377_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def banded(n, half, seed=3):
+    """Rows reaching every column within `half`: 2 * half + 1 slots."""
+    rng = np.random.default_rng(seed)
+    off = [sp.diags(-rng.uniform(0.1, 1.0, n - d), d) for d in range(1, half + 1)]
+    off = sp.csr_matrix(sum(off) + sum(o.T for o in off)) if off else sp.csr_matrix((n, n))
+    A = (off + sp.diags(1.2 * np.asarray(abs(off).sum(axis=1)).ravel() + 0.1)).tocsr()
+    A.sort_indices()
+    return W.CSRSystem(A.indptr.astype(np.int32), A.indices.astype(np.int32), A.data, rng.uniform(-1, 1, (1, n)))
+
+
+def with_rhs(s, r):
+    if r > 1:
+        s.b = np.random.default_rng(9).uniform(-1, 1, (r, s.n))
+    return s
+
+
+# (system, split, parts, subdomains, right-hand sides): one tile, ragged last
+# slices and tiles, each slot width (7, 14, 27), table and explicit columns
+CASES = {
+    "one-row": (lambda: banded(1, 0), 1, 1, None, 1),
+    "one-tile": (lambda: banded(65, 1), 1, 1, None, 1),
+    "tile-edge": (lambda: banded(512, 3), 1, 1, None, 1),
+    "tile-edge-plus": (lambda: banded(513, 3), 1, 1, None, 2),
+    "width-9": (lambda: banded(1500, 4), 1, 2, None, 1),
+    "width-15": (lambda: banded(1100, 7), 2, 3, None, 1),
+    "width-27": (lambda: banded(2000, 13), 1, 2, None, 4),
+    "bands": (lambda: W.laplace7(13, workload=1), 1, 3, None, 1),
+    "lists": (lambda: W.laplace7(17, workload=1), 2, 5, None, 2),
+    "sub": (lambda: W.laplace7(16, workload=1), 3, 4, (2, 2, 2), 4),
+    "fe-bands": (lambda: W.fe27(14, workload=3), 1, 3, None, 1),
+    "fe-lists": (lambda: W.fe27(22, workload=3), 2, 4, None, 1),
+    "fe-sub": (lambda: W.fe27(15, workload=3), 3, 4, (2, 2, 1), 2),
+    "cube-sub": (lambda: W.fe_q1_cube(17), 3, 4, (2, 2, 2), 1),
+}
+
+
+def pair(name):
+    build, mode, P, sub, r = CASES[name]
+    s = with_rhs(build(), r)
+    b = B()
+    return s, r, [make(s, mode, P, sub, opts={b.JAC_OPT_GRID: g}) for g in (1, 0)]
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_resident_loop_matches_per_sweep_launches(name):
+    need_gpu()
+    b = B()
+    s, r, hs = pair(name)
+    x0 = np.random.default_rng(5).uniform(-1, 1, (r, s.n))
+    out = []
+    for h in hs:
+        set_x(h, x0)
+        res = [sweep(h, 37, r), get_x(h, s.n, r)]
+        if h is hs[1]:
+            info = b.jac_get_info(h)
+            assert info["loop_grid"] == info["ntiles"] + 4        # the resident loop ran: four deciding workgroups
+        res.append(sweep(h, 7, r))                                # too short for it
+        for norm in (b.JAC_NORM_L2_REL, b.JAC_NORM_INF_ABS):
+            b.jac_set_x(h, None)
+            st, sw, rr = b.jac_solve(h, 1e-9, 20000, norm)
+            assert st == b.JAC_OK
+            res += [sw, rr, get_x(h, s.n, r)]
+        for maxit in (0, 8, 9, 20):                               # stops at the last residual
+            b.jac_set_x(h, None)
+            st, sw, rr = b.jac_solve(h, 0.0, maxit)
+            res += [np.array(st), sw, rr, get_x(h, s.n, r)]
+        b.jac_set_x(h, None)
+        st, sw, rr = b.jac_solve(h, 1e-11, 4000, b.JAC_NORM_L2_REL, b.JAC_FP32_REFINE)
+        res += [np.array(st), sw, rr, get_x(h, s.n, r)]
+        out.append(res)
+        b.jac_destroy(h)
+    for k, (u, v) in enumerate(zip(*out)):
+        assert np.array_equal(u, v), (name, k)
+    for c in range(r):
+        _, xr, hr = ref.sweeps(s.row_ptr, s.col_idx, s.vals, s.b[c], 37, x0=x0[c])
+        assert rel_inf(out[1][1][c], xr) <= 1e-12
+        assert np.all(np.abs(out[1][0][:, c] - hr) <= 1e-12 * np.maximum(hr, hr[0] * 1e-3))
+
+
+def test_stop_at_once_and_divergence():
+    need_gpu()
+    b = B()
+    s = W.laplace7(12, workload=1)
+    bad = W.CSRSystem(s.row_ptr, s.col_idx, np.where(s.vals > 0, 0.5, s.vals), s.b, grid=s.grid)
+    out = []
+    for g in (1, 0):
+        h = make(s, 1, 2, opts={b.JAC_OPT_GRID: g})
+        b.jac_set_rhs(h, torch.zeros(s.n, dtype=torch.float64, device="cuda"))
+        st, sw, rr = b.jac_solve(h, 1e-8, 1000)                   # b = 0, x = 0: x_0 passes
+        assert (st, int(sw[0]), float(rr[0])) == (b.JAC_OK, 0, 0.0)
+        b.jac_destroy(h)
+        h = make(bad, 1, 2, opts={b.JAC_OPT_GRID: g})
+        with pytest.raises(b.JacError) as e:
+            b.jac_solve(h, 1e-8, 100000)
+        assert e.value.status == b.JAC_E_DIVERGED
+        out.append(get_x(h, s.n))
+        b.jac_destroy(h)
+    assert np.array_equal(out[0], out[1])
+
+
+def test_many_launches_on_one_handle_after_a_new_split():
+    # control words and ring are reused launch after launch, also when a new
+    # split or precision lays them out differently
+    need_gpu()
+    b = B()
+    s = W.laplace7(14, workload=1)
+    h, hr = make(s, 1, 2), make(s, 1, 2, opts={b.JAC_OPT_GRID: 1})
+    for k in range(12):
+        mode, sub = ((1, None), (2, None), (3, (2, 2, 1)))[k % 3]
+        got = []
+        for hh in (h, hr):
+            b.jac_partition(hh, mode, 4, sub)
+            b.jac_set_x(hh, None)
+            st, sw, rr = b.jac_solve(hh, 1e-6, 5000, b.JAC_NORM_L2_REL, b.JAC_FP32_REFINE if k % 2 else b.JAC_FP64)
+            got.append((st, int(sw[0]), float(rr[0]), sweep(hh, 10 + k), get_x(hh, s.n)))
+        assert got[0][:3] == got[1][:3]
+        assert np.array_equal(got[0][3], got[1][3]) and np.array_equal(got[0][4], got[1][4])
+    b.jac_destroy(h)
+    b.jac_destroy(hr)
+
+
+def test_threads_on_streams_of_their_own():
+    need_gpu()
+    b = B()
+    s = W.laplace7(18, workload=1)
+    h = make(s, 2, 3, opts={b.JAC_OPT_GRID: 1})
+    b.jac_solve(h, 1e-8, 5000)
+    want = get_x(h, s.n)
+    b.jac_destroy(h)
+    got, errors = [None] * 3, []
+
+    def work(q):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                hh = make(s, 2, 3)
+                for _ in range(3):
+                    b.jac_set_x(hh, None)
+                    b.jac_solve(hh, 1e-8, 5000)
+                x = torch.empty(s.n, dtype=torch.float64, device="cuda")
+                b.jac_get_x(hh, x)
+                torch.cuda.current_stream().synchronize()
+                got[q] = x.cpu().numpy()
+                b.jac_destroy(hh)
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    ts = [threading.Thread(target=work, args=(q,)) for q in range(3)]
+    [t.start() for t in ts]
+    [t.join(60) for t in ts]
+    assert not errors
+    for g in got:
+        assert np.array_equal(g, want[0])
