@@ -69,6 +69,10 @@ static void build_transpose(Handle& h)
     if (t.colfmt == COL_TABG) up(h.td.shift, t.shift.data(), t.shift.size() * 4);
     else if (t.colfmt == COL_REL16) up(h.td.col16, t.col16.data(), t.col16.size() * 2);
     else up(h.td.col32, t.col32.data(), t.col32.size() * 4);
+    std::vector<int32_t> res;
+    for (const std::vector<int32_t>* v : {&t.res_run0, &t.res_run_lds, &t.res_run_delta, &t.res_fp, &t.res_own, &t.res_shift})
+        res.insert(res.end(), v->begin(), v->end());
+    up(h.td.res_plan, res.data(), t.res_run0.empty() ? 0 : res.size() * 4);
     up(h.td.t_map, mapT.data(), mapT.size() * 4);
     h.td.val.alloc((size_t)t.slots * sizeof(double));
     // The gradient pass reads x at global columns of A's slots: a staged plan
@@ -157,8 +161,18 @@ static void forward_ckpt(Handle& h, int32_t K, int32_t c)
     DeviceArrays& d = h.d;
     d.adj_ck.ensure(std::max<size_t>((all ? (size_t)(K + 1) : (size_t)nseg) * vec, 16));
     const SysDev sA = h.sysdev(false);
+    h.ckpt_K = -1;
     if (all) {
         auto CK = [&](int j) { return static_cast<double*>(d.adj_ck.p) + (size_t)j * n; };
+        SysState none;
+        launch_gather_in(nullptr, static_cast<const int32_t*>(d.perm.p), n, 1, CK(0), st);
+        if (run_resident(h, sA, false, false, K, 0, nullptr, nullptr, d.x1.p, d.x0.p, none, CK(0))) {
+            h.ckpt_K = K;
+            h.ckpt_c = c;
+            h.ckpt_all = true;
+            h.ckpt_gen = h.state_gen;
+            return;
+        }
         std::vector<SysDev> fs((size_t)std::max(K, 1), sA);
         for (int32_t k = 0; k < K; ++k) {
             fs[k].x[0] = CK(k);
@@ -173,7 +187,6 @@ static void forward_ckpt(Handle& h, int32_t K, int32_t c)
         const int fpb = h.lds_fp_bytes(false), tab = h.lds_tab();
         const size_t lds = loop_lds_bytes(fpb, tab, 0);
         const int grid = sweep_grid(h, fn, h.opt.block, lds);
-        launch_gather_in(nullptr, static_cast<const int32_t*>(d.perm.p), n, 1, CK(0), st);
         launch_init_state(static_cast<SysState*>(d.state.p), 1, st);
         for (int32_t k = 0; k < K; ++k) {
             // sweep 0 of its own descriptor: reads x[0], writes x[1], decides nothing
@@ -339,12 +352,33 @@ extern "C" jac_status jac_adjoint(jac_handle hp, int32_t K, int32_t ckpt, const 
             double* lin = static_cast<double*>(d.adj_lam0.p);
             double* lout = static_cast<double*>(d.adj_lam1.p);
             launch_gather_in(gx_dev, static_cast<const int32_t*>(d.perm.p), n, 1, lin, st);
+            // every mu kept: the reverse sweeps run in one resident launch,
+            // then one gradient pass per segment (the same sums in the same
+            // order as segment by segment)
+            bool reversed = false;
+            if (all && adjoint_bytes(h, K, c, true) + (size_t)K * vec <= ((size_t)h.opt.ckpt_mb << 20)) {
+                bool room = true;
+                try {
+                    d.adj_mu.ensure((size_t)K * vec);
+                } catch (const Error& e) {
+                    if (e.status != JAC_E_NOMEM) throw;
+                    (void)hipGetLastError();
+                    room = false;
+                }
+                double* mu = static_cast<double*>(d.adj_mu.p);
+                if (room && run_resident_adjoint(h, K, lin, mu, static_cast<double*>(d.adj_gb.p))) {
+                    for (int32_t j = nseg - 1; j >= 0; --j)
+                        launch_adj_grad(gfmt, h.plan.ntiles, st, d_sG, CK(j * c), mu + (size_t)j * c * n,
+                                        std::min(c, K - j * c), static_cast<double*>(d.adj_G.p));
+                    reversed = true;
+                }
+            }
             const int32_t Llast = K - (nseg - 1) * c;
-            launch_adj_init(static_cast<const double*>(d.invd.p), lin, n, Mm(Llast - 1),
+            if (!reversed) launch_adj_init(static_cast<const double*>(d.invd.p), lin, n, Mm(Llast - 1),
                             static_cast<double*>(d.adj_gb.p), st);
             // the recompute launches decide nothing (sweep 0 of a fresh state)
             launch_init_state(static_cast<SysState*>(d.state.p), 1, st);
-            for (int32_t j = nseg - 1; j >= 0; --j) {
+            for (int32_t j = nseg - 1; j >= 0 && !reversed; --j) {
                 const int32_t k0 = j * c;
                 const int32_t L = std::min(c, K - k0);
                 // x_{k0} .. x_{k0+L}: stored, or both ends known (checkpoints,

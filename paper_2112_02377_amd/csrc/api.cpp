@@ -124,7 +124,7 @@ void Handle::replan(int mode, int32_t nparts, const int32_t* sub_grid)
         prm.lds_elems = (int32_t)std::min<int64_t>(opt.lds_elems, cap);
     }
     prm.staged = (mode != JAC_BANDROW);
-    prm.fill_gap = mode == JAC_BANDROW_SP ? 2 : 0;
+    prm.fill_gap = mode == JAC_BANDROW_SP ? 16 : 0;
     prm.tables = opt.tables != 0;
     Plan pl = make_plan(pa, np.cuts, prm);
     // caller entry -> slot

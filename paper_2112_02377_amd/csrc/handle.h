@@ -69,7 +69,7 @@ struct DeviceArrays {
     // adjoint: A^T slot map, A's global columns (staged plans), and the
     // working buffers, kept between calls (grow-only)
     DevMem t_map, a_gcol;
-    DevMem adj_ck, adj_X, adj_M, adj_lam0, adj_lam1, adj_carry, adj_gb, adj_G, adj_sys, adj_segs, adj_fsegs;
+    DevMem adj_mu, adj_ck, adj_X, adj_M, adj_lam0, adj_lam1, adj_carry, adj_gb, adj_G, adj_sys, adj_segs, adj_fsegs;
     // resident loop: LDS layout of unstaged shift tables (the plan's res_
     // arrays one after another), and one buffer for the ring of iterates,
     // norm partials, descriptor and control words
@@ -147,9 +147,13 @@ void run_loop(Handle& h, std::vector<SysDev>& sys, bool fp32, bool solve, int32_
 // loop is too short or an option asks for per-sweep launches, or when the
 // launch gave up; the caller then runs run_loop.  Else the iterate is in
 // xout -- copied to x0_out when given -- and st holds the stop sweeps and
-// norms (solve mode).
+// norms (solve mode).  xall: receives x_{k+1} at (k + 1) * n of every sweep
+// (fixed sweeps, one column).
 bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t kend, int norm_inf, double* hist,
-                  const void* x0, void* xout, void* x0_out, SysState& st);
+                  const void* x0, void* xout, void* x0_out, SysState& st, double* xall = nullptr);
+// K reverse sweeps of the adjoint in one launch, on the plan of A^T: lam is
+// lambda_K, mu receives mu_k at (k - 1) * n for k = 1 .. K, gb their sum.
+bool run_resident_adjoint(Handle& h, int32_t K, const double* lam, double* mu, double* gb);
 jac_status solve_refine(Handle& h, double tol, int32_t maxit, int norm, int32_t* sweeps_out, double* relres_out);
 void set_last_error(const std::string& m);
 

@@ -193,7 +193,7 @@ Plan make_plan(const Csr& a, const std::vector<int32_t>& cuts_in, const PlanPara
     // shifts the LDS positions behind it, so that a slice reaches its columns
     // through more shifts, each a padded slot for all its rows (80^3 27-point
     // matrix with a tenth of its edges dropped: 30 slots in the widest slices,
-    // 27 with holes of up to two columns staged).
+    // 27 with the holes staged).
     if (prm.staged && prm.tables && tab_bytes < ell_bytes && max_tab_width > kResWidth &&
         max_tab_width <= kResWidth + 13 && prm.fill_gap > 0) {
         const std::vector<Footprint> plain = fps;

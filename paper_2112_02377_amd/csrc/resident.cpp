@@ -36,46 +36,52 @@ size_t res_lds(const Plan& pl, int32_t ldx, int nrhs, size_t elem, int width, bo
     return std::max({x + b, (size_t)pl.res_max_runs * 8, decider});
 }
 
-}  // namespace
+// What a launch needs besides its system; ok: the plan fits the chip and the
+// handle's options leave the choice open.
+struct ResLaunch {
+    bool ok = false;
+    void* fn = nullptr;
+    int grid = 0;
+    size_t lds = 0;
+    int32_t ldx = 0;
+    ResParams p{};
+};
 
-bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t kend, int norm_inf, double* hist,
-                  const void* x0, void* xout, void* x0_out, SysState& out)
+ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp32, int nrhs, int32_t kend, bool adjoint)
 {
-    const Plan& pl = h.plan;
-    const int nrhs = h.nrhs;
+    ResLaunch L;
     // Options that name a launch shape keep per-sweep launches (or the
     // persistent loop); the norm is summed in the order of 256 threads.
-    if (h.opt.loop != 0 || h.opt.grid != 0 || h.opt.block != kResBlock || kend < kResMinSweeps || h.res_off)
-        return false;
+    if (h.opt.loop != 0 || h.opt.grid != 0 || h.opt.block != kResBlock || kend < kResMinSweeps || h.res_off) return L;
     const bool loc = pl.colfmt == COL_LOCAL16;
-    if (!loc && pl.colfmt != COL_TABL && !(pl.colfmt == COL_TABG && !pl.res_run0.empty())) return false;
+    const bool tabg = pl.colfmt == COL_TABG && !pl.res_run0.empty();
+    if (!tabg && (adjoint || (!loc && pl.colfmt != COL_TABL))) return L;
     const int per_wave = (pl.max_tile_slices + kResBlock / 64 - 1) / (kResBlock / 64);
-    if (pl.ntiles < 1 || pl.max_width > kResWidth) return false;
+    if (pl.ntiles < 1 || pl.max_width > kResWidth) return L;
     // rows of more entries gathered than the width's kernel holds take the next wider one
     int width = pl.max_width;
     if (pl.res_max_halo > res_halo(width) * kResBlock) width = std::max(width, 8);
-    if (pl.res_max_halo > res_halo(width) * kResBlock) return false;
+    if (pl.res_max_halo > res_halo(width) * kResBlock) return L;
     const size_t ts = fp32 ? 4 : 8, vec = (size_t)h.a.n * nrhs * ts;
-    if (vec >= ((size_t)1 << 32)) return false;
-    void* fn = res_kernel(fp32, nrhs, width, per_wave, loc);
-    if (!fn) return false;
-    const int32_t ldx = pl.res_max_fp + (!loc && width > 14 ? 128 : 0);   // zeros at both ends, see resident.hip
-    if ((size_t)ldx * ts > 65536) return false;          // 16-bit byte offsets
+    if (vec >= ((size_t)1 << 32)) return L;              // 32-bit byte offsets into a ring slot
+    L.fn = adjoint ? res_adjoint_kernel(width, per_wave) : res_kernel(fp32, nrhs, width, per_wave, loc);
+    if (!L.fn) return L;
+    L.ldx = pl.res_max_fp + (!loc && width > 14 ? 128 : 0);   // zeros at both ends, see resident.hip
+    if ((size_t)L.ldx * ts > 65536) return L;            // 16-bit byte offsets
     // LDS is handed out in pieces of 1280 bytes, which the occupancy query
     // does not count; every workgroup must be resident, so round up here
-    const size_t lds = (res_lds(pl, ldx, nrhs, ts, width, loc) + 1279) / 1280 * 1280;
+    L.lds = (res_lds(pl, L.ldx, nrhs, ts, width, loc) + 1279) / 1280 * 1280;
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kResBlock, lds) != hipSuccess) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, L.fn, kResBlock, L.lds) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return L;
     }
-    const int64_t grid = (int64_t)pl.ntiles + kResDeciders;
-    if (grid > (int64_t)nb * num_cus()) return false;
+    L.grid = pl.ntiles + kResDeciders;
+    if (L.grid > (int64_t)nb * num_cus()) return L;
 
     DeviceArrays& d = h.d;
-    hipStream_t st = h.stream;
     const int npart = res_partials(nrhs, width, loc);
-    const size_t o_ring = kResRingOff, o_part = o_ring + up256((size_t)kResRing * vec);
+    const size_t o_part = kResRingOff + up256((size_t)kResRing * vec);
     const size_t bytes = o_part + (size_t)kResPart * pl.ntiles * npart * nrhs * sizeof(double);
     if (!d.res_work.p || d.res_work.bytes < bytes) {
         try {
@@ -83,20 +89,19 @@ bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t ken
         } catch (const Error& e) {
             if (e.status != JAC_E_NOMEM) throw;
             (void)hipGetLastError();
-            return false;                   // per-sweep launches need none of it
+            return L;                       // per-sweep launches need none of it
         }
-        launch_zero_u32(static_cast<uint32_t*>(d.res_work.p), (int32_t)(sizeof(ResCtl) / 4), st);
+        launch_zero_u32(static_cast<uint32_t*>(d.res_work.p), (int32_t)(sizeof(ResCtl) / 4), h.stream);
         h.res_next = kResPart;
         h.res_arrived = 0;
     }
     char* work = static_cast<char*>(d.res_work.p);
-    ResCtl* dev = reinterpret_cast<ResCtl*>(work);
-    ResSys r{};
-    r.tile_row0 = s.tile_row0;
-    r.tile_slice0 = s.tile_slice0;
-    r.slice_off = s.slice_off;
-    if (pl.colfmt == COL_TABG) {
-        const int32_t* q = static_cast<const int32_t*>(d.res_plan.p);
+    ResSys& r = L.p.sys;
+    r.tile_row0 = static_cast<const int32_t*>(pd.tile_row0.p);
+    r.tile_slice0 = static_cast<const int32_t*>(pd.tile_slice0.p);
+    r.slice_off = static_cast<const int64_t*>(pd.slice_off.p);
+    if (tabg) {
+        const int32_t* q = static_cast<const int32_t*>(pd.res_plan.p);
         r.run0 = q;
         r.run_lds = q += pl.res_run0.size();
         r.run_delta = q += pl.res_run_lds.size();
@@ -104,48 +109,47 @@ bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t ken
         r.own = q += pl.res_fp.size();
         r.shift = q += pl.res_own.size();
     } else {
-        r.run0 = s.tile_run0;
-        r.run_lds = s.run_lds;
-        r.run_delta = s.run_delta;
-        r.fp = s.tile_fp;
-        r.own = s.tile_own;
-        r.shift = s.shift;
+        r.run0 = static_cast<const int32_t*>(pd.tile_run0.p);
+        r.run_lds = static_cast<const int32_t*>(pd.run_lds.p);
+        r.run_delta = static_cast<const int32_t*>(pd.run_delta.p);
+        r.fp = static_cast<const int32_t*>(pd.tile_fp.p);
+        r.own = static_cast<const int32_t*>(pd.tile_own.p);
+        r.shift = static_cast<const int32_t*>(pd.shift.p);
     }
-    r.col16 = s.col16;
-    r.val = s.val;
-    r.b = s.b;
-    r.x0 = x0;
-    r.xout = xout;
-    r.ring = work + o_ring;
+    r.col16 = static_cast<const uint16_t*>(pd.col16.p);
+    r.ring = work + kResRingOff;
     r.part = reinterpret_cast<double*>(work + o_part);
-    r.ctl = dev;
+    r.ctl = reinterpret_cast<ResCtl*>(work);
     r.n = h.a.n;
     r.ntiles = pl.ntiles;
-    for (int c = 0; c < 4; ++c) {
-        r.thr[c] = s.thr[c];
-        r.big[c] = s.big[c];
-    }
-    ResParams p{};
-    p.sys = r;
-    p.hist = hist;
-    p.kbase = h.res_next;
-    p.arrive = h.res_arrived += (uint32_t)grid;
-    p.nd = kResDeciders;
-    p.kend = kend;
-    p.solve = solve ? 1 : 0;
-    p.norm_inf = norm_inf;
+    L.p.kend = kend;
+    L.p.nd = kResDeciders;
+    L.ok = true;
+    return L;
+}
+
+// Runs it and waits; false (and not tried again) if the launch was refused
+// or gave up.
+bool res_run(Handle& h, ResLaunch& L, ResCtl& host, const void* from, void* to, bool fp32, int64_t m)
+{
+    L.p.kbase = h.res_next;
+    L.p.arrive = h.res_arrived + (uint32_t)L.grid;
     if (h.opt.timing) {
         for (auto& e : h.ev)
             if (!e) JAC_HIP(hipEventCreate(&e));
-        JAC_HIP(hipEventRecord(h.ev[0], st));
+        JAC_HIP(hipEventRecord(h.ev[0], h.stream));
     }
-    launch_res(fn, (int)grid, lds, ldx, st, p);
-    if (h.opt.timing) JAC_HIP(hipEventRecord(h.ev[1], st));
-    if (x0_out) launch_res_settle(fp32, st, xout, x0_out, (int64_t)h.a.n * nrhs, dev, p.kbase);
-    ResCtl host;
-    JAC_HIP(hipMemcpyAsync(&host, dev, sizeof(ResCtl), hipMemcpyDeviceToHost, st));
+    if (launch_res(L.fn, L.grid, L.lds, L.ldx, h.stream, L.p) != hipSuccess) {
+        (void)hipGetLastError();
+        h.res_off = true;
+        return false;
+    }
+    h.res_arrived = L.p.arrive;
+    if (h.opt.timing) JAC_HIP(hipEventRecord(h.ev[1], h.stream));
+    if (to) launch_res_settle(fp32, h.stream, from, to, m, L.p.sys.ctl, L.p.kbase);
+    JAC_HIP(hipMemcpyAsync(&host, L.p.sys.ctl, sizeof(ResCtl), hipMemcpyDeviceToHost, h.stream));
     h.sync();
-    if (host.abort == p.kbase) {
+    if (host.abort == L.p.kbase) {
         h.res_off = true;                   // do not wait that long again
         return false;
     }
@@ -155,17 +159,59 @@ bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t ken
         h.last_loop_ms = ms;
     }
     // no word of this launch lies beyond its last sweep by more than the tiles run ahead
-    h.res_next = p.kbase + (uint32_t)(solve ? host.last_k : kend) + 2 * kResPart;
-    h.last_grid = (int)grid;
+    h.res_next = L.p.kbase + (uint32_t)(L.p.solve ? host.last_k : L.p.kend) + 2 * kResPart;
+    return true;
+}
+
+}  // namespace
+
+bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t kend, int norm_inf, double* hist,
+                  const void* x0, void* xout, void* x0_out, SysState& out, double* xall)
+{
+    ResLaunch L = res_prepare(h, h.plan, h.d, fp32, h.nrhs, kend, false);
+    if (!L.ok) return false;
+    ResSys& r = L.p.sys;
+    r.val = s.val;
+    r.b = s.b;
+    r.x0 = x0;
+    r.xout = xout;
+    for (int c = 0; c < 4; ++c) {
+        r.thr[c] = s.thr[c];
+        r.big[c] = s.big[c];
+    }
+    L.p.hist = hist;
+    L.p.xall = xall;
+    L.p.solve = solve ? 1 : 0;
+    L.p.norm_inf = norm_inf;
+    ResCtl host;
+    if (!res_run(h, L, host, xout, x0_out, fp32, (int64_t)h.a.n * h.nrhs)) return false;
+    h.last_grid = L.grid;
     h.last_loop_sweeps = kend;
     for (int c = 0; c < 4; ++c) {
-        out.stop_k[c] = (int32_t)(host.stop[c] - p.kbase);
+        out.stop_k[c] = (int32_t)(host.stop[c] - L.p.kbase);
         out.nrm[c] = host.nrm[c];
     }
     out.done_k = 0;
     out.status = host.status;
     out.last_k = host.last_k;
     return true;
+}
+
+bool run_resident_adjoint(Handle& h, int32_t K, const double* lam, double* mu, double* gb)
+{
+    ResLaunch L = res_prepare(h, h.tplan, h.td, false, 1, K - 1, true);
+    if (!L.ok) return false;
+    ResSys& r = L.p.sys;
+    r.val = h.td.val.p;
+    r.b = lam;
+    r.invd = h.d.invd.p;
+    r.xout = gb;
+    L.p.xall = mu;
+    ResCtl host;
+    const double ms = h.last_loop_ms;
+    const bool ok = res_run(h, L, host, nullptr, nullptr, false, 0);
+    h.last_loop_ms = ms;                    // the forward's
+    return ok;
 }
 
 }  // namespace jac

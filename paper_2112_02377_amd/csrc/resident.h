@@ -66,7 +66,8 @@ struct ResSys {
     const int32_t* shift;           // shift-table splits: LDS position minus row, per slot column
     const uint16_t* col16;          // explicit splits: LDS position per slot
     const void* val;                // slot values, T
-    const void* b;                  // T, node-major [n][nrhs]
+    const void* b;                  // T, node-major [n][nrhs] (adjoint: lambda_K)
+    const void* invd;               // adjoint: D^{-1}
     const void* x0;                 // starting iterate, T (null: zero)
     void* xout;                     // returned iterate, T
     void* ring;                     // T [kResRing][nrhs][n]: iterates as their tiles publish them
@@ -80,6 +81,9 @@ struct ResSys {
 struct ResParams {
     ResSys sys;
     double* hist;                   // nullable, [k * nrhs + c]
+    // nullable: every iterate, x_k at k * n (fixed sweeps of one FP64 column);
+    // adjoint: mu of the kend + 1 steps, the first (mu_K) last
+    void* xall;
     uint32_t kbase;                 // see ResCtl
     uint32_t arrive;                // ctl->arrived once every workgroup of this launch has arrived
     int32_t nd;                     // deciding workgroups (1, 2, 4 or 8)
@@ -88,8 +92,10 @@ struct ResParams {
 
 // Kernel for slots per row (7, 14 or 28) and slices per wave (2 or 4), or null when there is none.
 void* res_kernel(bool fp32, int nrhs, int width, int slices, bool explicit_cols);
+// Reverse sweeps of the adjoint (FP64, one column, shift table).
+void* res_adjoint_kernel(int width, int slices);
 // ldx: x entries in LDS per right-hand side; lds: see res_lds in resident.cpp
-void launch_res(void* fn, int grid, size_t lds, int32_t ldx, hipStream_t st, ResParams p);
+hipError_t launch_res(void* fn, int grid, size_t lds, int32_t ldx, hipStream_t st, ResParams p);
 // x0 = xout unless the launch gave up
 void launch_res_settle(bool fp32, hipStream_t st, const void* xout, void* x0, int64_t m, const ResCtl* ctl,
                        uint32_t kbase);

@@ -229,43 +229,50 @@ __device__ void res_decide(const ResParams& P, int32_t d, double* red)
                     event = true;
             }
             if (event) {
-                // earlier sweeps decide first
+                // earlier sweeps decide first -- unless one of them has stopped
+                // the last column, after which the others may have left
                 Patience w2;
-                for (int32_t j = max(0, k - P.nd + 1); j < k; ++j)
-                    while ((int32_t)(ldc(&ctl->word[j & (P.nd - 1)]) - kbase) < j)
-                        if (w2.out(ctl, kbase)) break;
-                asm volatile("" ::: "memory");
-                int32_t st[NRHS];
-                bool diverged = false, exhausted = false, running = false;
+                bool over = false;
+                for (int32_t j = max(0, k - P.nd + 1); j < k && !over; ++j)
+                    while ((int32_t)(ldc(&ctl->word[j & (P.nd - 1)]) - kbase) < j) {
+                        over = ldc(&ctl->done) == kbase || w2.out(ctl, kbase);
+                        if (over) break;
+                    }
+                if (over) stopped = (1u << NRHS) - 1u;
+                else {
+                    asm volatile("" ::: "memory");
+                    int32_t st[NRHS];
+                    bool diverged = false, exhausted = false, running = false;
 #pragma unroll
-                for (int c = 0; c < NRHS; ++c) {
-                    st[c] = (int32_t)(ldc(&ctl->stop[c]) - kbase);
-                    if (st[c] >= 0) continue;
-                    st[c] = kNever;
-                    stc(&ctl->nrm[c], nrm[c]);
-                    if (!(nrm[c] <= S.big[c])) diverged = true;
-                    else if (nrm[c] <= S.thr[c]) st[c] = k;
-                    else if (k >= P.kend) { st[c] = k; exhausted = true; }
-                    else running = true;
-                }
-                if (diverged) {
+                    for (int c = 0; c < NRHS; ++c) {
+                        st[c] = (int32_t)(ldc(&ctl->stop[c]) - kbase);
+                        if (st[c] >= 0) continue;
+                        st[c] = kNever;
+                        stc(&ctl->nrm[c], nrm[c]);
+                        if (!(nrm[c] <= S.big[c])) diverged = true;
+                        else if (nrm[c] <= S.thr[c]) st[c] = k;
+                        else if (k >= P.kend) { st[c] = k; exhausted = true; }
+                        else running = true;
+                    }
+                    if (diverged) {
 #pragma unroll
-                    for (int c = 0; c < NRHS; ++c)
-                        if (st[c] >= k) st[c] = k;
-                    running = false;
-                    stc(&ctl->status, (int32_t)JAC_E_DIVERGED);
-                } else if (exhausted && ldc(&ctl->status) == JAC_OK) {
-                    stc(&ctl->status, (int32_t)JAC_NOT_CONVERGED);
-                }
-                stc(&ctl->last_k, k);
+                        for (int c = 0; c < NRHS; ++c)
+                            if (st[c] >= k) st[c] = k;
+                        running = false;
+                        stc(&ctl->status, (int32_t)JAC_E_DIVERGED);
+                    } else if (exhausted && ldc(&ctl->status) == JAC_OK) {
+                        stc(&ctl->status, (int32_t)JAC_NOT_CONVERGED);
+                    }
 #pragma unroll
-                for (int c = 0; c < NRHS; ++c) {
-                    if (st[c] == kNever) continue;
-                    stc(&ctl->stop[c], kbase + (uint32_t)st[c]);
-                    stopped |= 1u << c;
+                    for (int c = 0; c < NRHS; ++c) {
+                        if (st[c] == kNever) continue;
+                        if (st[c] == k) stc(&ctl->last_k, k);
+                        stc(&ctl->stop[c], kbase + (uint32_t)st[c]);
+                        stopped |= 1u << c;
+                    }
+                    wait_own();
+                    if (!running) stc(&ctl->done, kbase);
                 }
-                wait_own();
-                if (!running) stc(&ctl->done, kbase);
             }
             wait_own();
             stc(&ctl->word[d], kbase + (uint32_t)k);
@@ -291,7 +298,11 @@ __device__ void res_decide(const ResParams& P, int32_t d, double* red)
 // one straight run of code, so their gathers and sums overlap: a workgroup
 // has about one wave per SIMD and nothing else hides LDS latency.  Slots past
 // a slice's width hold zeros and repeat the position of its last one.
-template <typename T, int NRHS, int W, int SPL, bool LOC>
+//
+// ADJ: the reverse sweeps of the adjoint on the layout of A^T.  What is
+// exchanged is mu = D^{-1} lambda; lambda takes b's place (lambda -= A^T mu),
+// every mu is also stored for the gradient pass, and their sum is returned.
+template <typename T, int NRHS, int W, int SPL, bool LOC, bool ADJ>
 __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t ldx)
 {
     using U = typename Bits<T>::type;
@@ -359,6 +370,7 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
     uint2 cp[WIDE ? 1 : SPL][WIDE ? 1 : NC];        // positions of four slots each
     int32_t shv[TABW ? SPL : 1];                    // lane k: byte shift of slot k
     T bv[BL ? 1 : SPL][NRHS], di[SPL], xs[SPL][NRHS];
+    T sum[ADJ ? SPL : 1];                           // ADJ: the sum of mu
     {
         const cptr<const int64_t> slice_off = (cptr<const int64_t>)D->slice_off;
         const cptr<const int32_t> shift = (cptr<const int32_t>)D->shift;
@@ -408,13 +420,20 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
                     else cp[j][q] = p2;
                 }
             }
-            di[j] = (T)1 / d;
+            if constexpr (ADJ) di[j] = ((gptr<const T>)D->invd)[ib];
+            else di[j] = (T)1 / d;
 #pragma unroll
             for (int c = 0; c < NRHS; ++c) {
                 if constexpr (BL) lds_b[j * kResBlock + tid] = b[(int64_t)ib * NRHS + c];
                 else bv[j][c] = b[(int64_t)ib * NRHS + c];
                 xs[j][c] = (T)0;
-                if (D->x0) xs[j][c] = x0[(int64_t)ib * NRHS + c];
+                if constexpr (ADJ) {
+                    xs[j][c] = di[j] * b[ib];
+                    sum[j] = xs[j][c];
+                    if (i < r1) ((gptr<T>)P.xall)[(int64_t)P.kend * n + i] = xs[j][c];
+                } else if (D->x0) {
+                    xs[j][c] = x0[(int64_t)ib * NRHS + c];
+                }
             }
         }
     }
@@ -670,8 +689,16 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
 #pragma unroll
             for (int c = 0; c < NRHS; ++c) {
                 const T r = (BL ? lds_b[j * kResBlock + tv] : bv[BL ? 0 : j][c]) - q[j][c];
-                xo[j][c] = xo[j][c] + di[j] * r;
-                rd[j][c] = li < rows ? (double)r : 0.0;
+                if constexpr (ADJ) {
+                    if constexpr (BL) lds_b[j * kResBlock + tv] = r;
+                    else bv[j][c] = r;
+                    xo[j][c] = di[j] * r;
+                    sum[j] = __builtin_fma(di[j], r, sum[j]);   // as the per-step kernel contracts it
+                    rd[j][c] = 0.0;
+                } else {
+                    xo[j][c] = xo[j][c] + di[j] * r;
+                    rd[j][c] = li < rows ? (double)r : 0.0;
+                }
             }
         }
 #pragma unroll
@@ -683,6 +710,15 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
                 __builtin_memcpy(&w2, &xo[j][c], sizeof(T));
                 if (w2 == SENT) w2 ^= 1;            // never publish the sentinel itself
                 if (li < rows) sto(dst + (int64_t)c * n, (uint32_t)(r0 + li) * (uint32_t)sizeof(T), w2);
+            }
+        }
+        // iterates kept by the caller: x_{k+1}, or mu counted downwards
+        if (NRHS == 1 && sizeof(T) == 8 && P.xall) {
+            T* const keep = static_cast<T*>(P.xall) + (int64_t)(ADJ ? P.kend - 1 - k : k + 1) * n;
+#pragma unroll
+            for (int j = 0; j < SPL; ++j) {
+                const int32_t li = tv + j * kResBlock;
+                if (li < rows) __builtin_nontemporal_store(xo[j][0], (gptr<T>)keep + (r0 + li));
             }
         }
         // the wave's norm partial
@@ -777,7 +813,7 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
                 if (li < rows) {
 #pragma unroll
                     for (int c = 0; c < NRHS; ++c)
-                        reinterpret_cast<T*>(D->xout)[(int64_t)(r0 + li) * NRHS + c] = xo[j][c];
+                        reinterpret_cast<T*>(D->xout)[(int64_t)(r0 + li) * NRHS + c] = ADJ ? sum[ADJ ? j : 0] : xo[j][c];
                 }
             }
             return;
@@ -805,14 +841,14 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
 // Waves per SIMD asked of the compiler: what the registers held across a
 // sweep leave room for.
 template <typename T>
-constexpr int res_waves(int nrhs, int w, bool loc)
+constexpr int res_waves(int nrhs, int w, bool loc, bool adj)
 {
-    if (sizeof(T) == 8) return nrhs == 1 ? (w <= 7 ? 5 : 3) : nrhs == 2 ? (w <= 7 ? 4 : 2) : w <= 7 ? 3 : 1;
+    if (sizeof(T) == 8) return nrhs == 1 ? (w <= 7 ? (adj ? 4 : 5) : 3) : nrhs == 2 ? (w <= 7 ? 4 : 2) : w <= 7 ? 3 : 1;
     return nrhs == 1 ? (w <= 7 ? 7 : 5) : nrhs == 2 ? (w <= 7 ? 5 : 4) : w <= 7 ? 4 : 2;
 }
 
-template <typename T, int NRHS, int W, int SPL, bool LOC>
-__global__ void __launch_bounds__(kResBlock) __attribute__((amdgpu_waves_per_eu(res_waves<T>(NRHS, W, LOC))))
+template <typename T, int NRHS, int W, int SPL, bool LOC, bool ADJ>
+__global__ void __launch_bounds__(kResBlock) __attribute__((amdgpu_waves_per_eu(res_waves<T>(NRHS, W, LOC, ADJ))))
 k_resident(ResParams P, int32_t ldx)
 {
     extern __shared__ __align__(16) char smem[];
@@ -831,7 +867,7 @@ k_resident(ResParams P, int32_t ldx)
     }
     int32_t first, end, stride;
     xcd_items(ntiles, ntiles, wg, first, end, stride);
-    res_tile<T, NRHS, W, SPL, LOC>(P, first, smem, ldx);
+    res_tile<T, NRHS, W, SPL, LOC, ADJ>(P, first, smem, ldx);
 }
 
 template <typename U>
@@ -846,8 +882,8 @@ __global__ void __launch_bounds__(256) k_res_settle(const U* __restrict__ from, 
 template <typename T, int NRHS, int W, int SPL>
 void* pick_loc(bool loc)
 {
-    return loc ? reinterpret_cast<void*>(&k_resident<T, NRHS, W, SPL, true>)
-               : reinterpret_cast<void*>(&k_resident<T, NRHS, W, SPL, false>);
+    return loc ? reinterpret_cast<void*>(&k_resident<T, NRHS, W, SPL, true, false>)
+               : reinterpret_cast<void*>(&k_resident<T, NRHS, W, SPL, false, false>);
 }
 template <typename T, int NRHS>
 void* pick_shape(int width, int slices, bool loc)
@@ -872,16 +908,25 @@ void* pick_rhs(int nrhs, int width, int slices, bool loc)
 
 }  // namespace
 
+void* res_adjoint_kernel(int width, int slices)
+{
+    if (slices > 2) return nullptr;
+    if (width <= 7) return reinterpret_cast<void*>(&k_resident<double, 1, 7, 2, false, true>);
+    if (width <= 14) return reinterpret_cast<void*>(&k_resident<double, 1, 14, 2, false, true>);
+    if (width <= 27) return reinterpret_cast<void*>(&k_resident<double, 1, 27, 2, false, true>);
+    return nullptr;
+}
+
 void* res_kernel(bool fp32, int nrhs, int width, int slices, bool explicit_cols)
 {
     return fp32 ? pick_rhs<float>(nrhs, width, slices, explicit_cols)
                 : pick_rhs<double>(nrhs, width, slices, explicit_cols);
 }
 
-void launch_res(void* fn, int grid, size_t lds, int32_t ldx, hipStream_t st, ResParams p)
+hipError_t launch_res(void* fn, int grid, size_t lds, int32_t ldx, hipStream_t st, ResParams p)
 {
     void* args[] = {&p, &ldx};
-    JAC_HIP(hipLaunchCooperativeKernel(fn, dim3(grid), dim3(kResBlock), args, (unsigned)lds, st));
+    return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(kResBlock), args, (unsigned)lds, st);
 }
 
 void launch_res_settle(bool fp32, hipStream_t st, const void* xout, void* x0, int64_t m, const ResCtl* ctl,

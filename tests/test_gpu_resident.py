@@ -137,6 +137,23 @@ def test_many_launches_on_one_handle_after_a_new_split():
     b.jac_destroy(hr)
 
 
+def test_the_loop_keeps_running_after_many_stops():
+    # the workgroups that decide later sweeps must leave once an earlier sweep
+    # stopped the last column, whatever they were waiting for: a launch that
+    # runs out of patience sends its handle to per-sweep launches for good
+    need_gpu()
+    b = B()
+    for s, prec in ((W.laplace7(10, workload=1), b.JAC_FP32_REFINE), (W.fe27(9, workload=3), b.JAC_FP64)):
+        h = make(s, 1, 2)
+        for k in range(150):
+            b.jac_set_x(h, None)
+            st, sw, rr = b.jac_solve(h, 10.0 ** -(3 + k % 7), 5000, b.JAC_NORM_L2_REL, prec)
+            assert st == b.JAC_OK
+        info = b.jac_get_info(h)
+        assert info["loop_grid"] == info["ntiles"] + 4
+        b.jac_destroy(h)
+
+
 def test_threads_on_streams_of_their_own():
     need_gpu()
     b = B()
@@ -168,3 +185,30 @@ def test_threads_on_streams_of_their_own():
     assert not errors
     for g in got:
         assert np.array_equal(g, want[0])
+
+
+@pytest.mark.parametrize("name,K,c", [("bands", 40, 7), ("lists", 9, 20), ("fe-bands", 33, 11), ("cube-sub", 25, 25)])
+def test_adjoint_in_resident_launches(name, K, c):
+    # forward, reverse sweeps and gradient against per-sweep launches (bit for
+    # bit) and the oracle's full-storage reverse sweep (1e-10 relative to the
+    # incoming gradient, the bar of every adjoint path)
+    need_gpu()
+    b = B()
+    build, mode, P, sub, _ = CASES[name]
+    s = build()
+    g = np.random.default_rng(4).uniform(-1, 1, s.n)
+    out = []
+    for grid, mb in ((1, 4096), (0, 4096), (0, 4)):
+        h = make(s, mode, P, sub, opts={b.JAC_OPT_GRID: grid, b.JAC_OPT_CKPT_MEM_MB: mb})
+        gb = torch.empty(s.n, dtype=torch.float64, device="cuda")
+        gv = torch.empty(s.nnz, dtype=torch.float64, device="cuda")
+        b.jac_adjoint(h, K, c, torch.from_numpy(g).cuda(), gb, gv)
+        out.append((gb.cpu().numpy(), gv.cpu().numpy(), get_x(h, s.n)[0]))
+        b.jac_destroy(h)
+    for k, o in enumerate(out[1:]):
+        for u, v in zip(o, out[0]):
+            assert np.array_equal(u, v), (name, k)
+    _, gbo, gvo, xk = ref.adjoint(s.row_ptr, s.col_idx, s.vals, s.b[0], K, g)
+    scale = np.abs(g).max()
+    assert np.abs(out[1][0] - gbo).max() <= 1e-10 * scale and np.abs(out[1][1] - gvo).max() <= 1e-10 * scale
+    assert rel_inf(out[1][2], xk) <= 1e-12
