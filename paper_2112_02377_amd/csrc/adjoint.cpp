@@ -353,8 +353,8 @@ extern "C" jac_status jac_adjoint(jac_handle hp, int32_t K, int32_t ckpt, const 
             double* lout = static_cast<double*>(d.adj_lam1.p);
             launch_gather_in(gx_dev, static_cast<const int32_t*>(d.perm.p), n, 1, lin, st);
             // every mu kept: the reverse sweeps run in one resident launch,
-            // then one gradient pass per segment (the same sums in the same
-            // order as segment by segment)
+            // then the gradient of all segments in another (the same sums in
+            // the same order as segment by segment)
             bool reversed = false;
             if (all && adjoint_bytes(h, K, c, true) + (size_t)K * vec <= ((size_t)h.opt.ckpt_mb << 20)) {
                 bool room = true;
@@ -367,9 +367,8 @@ extern "C" jac_status jac_adjoint(jac_handle hp, int32_t K, int32_t ckpt, const 
                 }
                 double* mu = static_cast<double*>(d.adj_mu.p);
                 if (room && run_resident_adjoint(h, K, lin, mu, static_cast<double*>(d.adj_gb.p))) {
-                    for (int32_t j = nseg - 1; j >= 0; --j)
-                        launch_adj_grad(gfmt, h.plan.ntiles, st, d_sG, CK(j * c), mu + (size_t)j * c * n,
-                                        std::min(c, K - j * c), static_cast<double*>(d.adj_G.p));
+                    launch_adj_grad(gfmt, h.plan.ntiles, h.plan.max_tile_slices, st, d_sG, CK(0), mu, K, c,
+                                    static_cast<double*>(d.adj_G.p));
                     reversed = true;
                 }
             }
@@ -406,7 +405,8 @@ extern "C" jac_status jac_adjoint(jac_handle hp, int32_t K, int32_t ckpt, const 
                                     static_cast<double*>(d.adj_gb.p), static_cast<const double*>(d.invd.p));
                     std::swap(lin, lout);
                 }
-                launch_adj_grad(gfmt, h.plan.ntiles, st, d_sG, X0, Mm(0), L, static_cast<double*>(d.adj_G.p));
+                launch_adj_grad(gfmt, h.plan.ntiles, h.plan.max_tile_slices, st, d_sG, X0, Mm(0), L, L,
+                                static_cast<double*>(d.adj_G.p));
                 if (j > 0) JAC_HIP(hipMemcpyAsync(Mm(c - 1), d.adj_carry.p, vec, hipMemcpyDeviceToDevice, st));
             }
         }

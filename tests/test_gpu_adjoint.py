@@ -43,6 +43,24 @@ def test_adjoint_matches_full_storage_oracle(mode, P, sub, K, c):
     b.jac_destroy(h)
 
 
+@pytest.mark.parametrize("tile", [64, 448, 8192])
+def test_gradient_pass_over_tile_sizes(tile):
+    # tiles of one slice, of no multiple of a workgroup's four and of more
+    # slices than the launch has waves for; 7- and 27-entry rows (one batch
+    # and four), a last segment of its own length
+    need_gpu()
+    b = B()
+    for s in (W.diffusion_adjoint(23), W.fe27(15)):
+        K = 17
+        g = np.random.default_rng(6).uniform(-1, 1, s.n)
+        h = make(s, 1, 1, opts={b.JAC_OPT_TILE_ROWS: tile})
+        gb, gv = run_adjoint(h, K, 5, g, s.n, s.nnz)
+        _, gbo, gvo, _ = ref.adjoint(s.row_ptr, s.col_idx, s.vals, s.b[0], K, g)
+        assert np.abs(gb - gbo).max() <= 1e-10 * np.abs(gbo).max(), tile
+        assert np.abs(gv - gvo).max() <= 1e-10 * np.abs(gvo).max(), tile
+        b.jac_destroy(h)
+
+
 def test_adjoint_of_nonsymmetric_paper_example():
     need_gpu()
     from test_oracle_pins import fig_csr
