@@ -85,7 +85,13 @@ typedef enum {
                                 run lookup table and the reduction scratch fit
                                 the device's LDS per workgroup (160 KiB on
                                 gfx950)                                        */
-    JAC_OPT_LOOP = 4,        /* 0 = one launch per sweep (default), 1 = persistent
+    JAC_OPT_LOOP = 4,        /* 0 = (default) where the split's tiles all fit the
+                                device at once, the tile, block and grid
+                                options leave it open and a call has eight
+                                sweeps or more: every sweep in one resident
+                                launch, the call then waits for it; else one
+                                launch per sweep.  Iterates, norms and stop
+                                sweeps are the same bits.  1 = persistent
                                 cooperative loop with a grid barrier per sweep     */
     JAC_OPT_WG_PER_CU = 5,   /* persistent loop: workgroups per CU, default 2 (0 =
                                 as many as fit: 5 for the FP64 kernels)         */
@@ -120,7 +126,8 @@ typedef enum {
                                 column per slot, if that streams fewer bytes
                                 over the whole split; 0: never.  Results are
                                 bit-identical either way                       */
-    JAC_OPT_GRID = 13         /* workgroups of the one-launch-per-sweep loop of a
+    JAC_OPT_GRID = 13         /* 1 and 2 keep one launch per sweep.  Workgroups of
+                                the one-launch-per-sweep loop of a
                                 single system (each of the eight XCDs sweeps a
                                 contiguous share of the tiles of about equal
                                 streamed bytes): 1 = one per tile of the
@@ -146,7 +153,8 @@ typedef struct {
     int64_t staged_entries;      /* sum over tiles of staged x entries             */
     int64_t alg_bytes_per_sweep; /* 12 nnz + 4 (n+1) + 8 n + 24 n nrhs (CSR model)   */
     int64_t dev_bytes_per_sweep; /* bytes the kernel actually streams per sweep     */
-    int32_t loop_grid;           /* workgroups of the last sweep loop               */
+    int32_t loop_grid;           /* workgroups of the last sweep loop (resident
+                                    loop: one per tile and four that decide)        */
     int32_t block;               /* threads per workgroup                           */
     double last_loop_ms;         /* duration of the last sweep loop (JAC_OPT_TIMING) */
     int32_t last_loop_sweeps;    /* sweeps that loop ran (incl. a final test sweep)  */
@@ -328,7 +336,9 @@ jac_status jac_sweep_checkpointed(jac_handle h, int32_t K, int32_t ckpt_every);
  * iterate and nothing is recomputed; otherwise it keeps every
  * ckpt_every-th iterate (ceil(K/ckpt_every) + 2*ckpt_every + 5 vectors plus
  * one double per slot, else JAC_E_INVALID) and each segment is swept again
- * from its checkpoint.  Both give bit-identical results.  The forward pass
+ * from its checkpoint.  Where K more vectors fit as well and the resident
+ * loop takes the split, every mu is kept and the reverse sweeps and the
+ * gradient are one launch each.  All give bit-identical results.  The forward pass
  * is skipped when jac_sweep_checkpointed left valid iterates for this K and
  * stride.  Leaves x = x_K in the handle.  Either output may be NULL.  The
  * buffers stay with the handle for later calls until jac_destroy. */

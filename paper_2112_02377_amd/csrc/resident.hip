@@ -9,7 +9,9 @@
 // What bounds a sweep is then the trip of a value from one workgroup to
 // another through device-coherent memory (about 1.0-1.5 us measured with up
 // to 256 workgroups, 1.8 us with 512), where a launch per sweep costs
-// 5.4 us at 20^3 and 6.8 us at 64^3.
+// 5.4 us at 20^3 and 6.8 us at 64^3.  Whole solves, a launch per sweep against
+// this loop: 20^3 Laplacian 7.10 and 2.95 ms, 33^3 and 65^3 Q1 cubes 6.54 and
+// 2.40, 39.2 and 12.1 ms, 56^3 27-point matrix 4.87 and 1.67 ms.
 //
 // Exchange without fences or barriers across workgroups: x_k is published in
 // slot k mod 8 of a ring with relaxed device-scope stores, one per value.  A
