@@ -66,7 +66,7 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     if (vec >= ((size_t)1 << 32)) return L;              // 32-bit byte offsets into a ring slot
     L.fn = adjoint ? res_adjoint_kernel(width, per_wave) : res_kernel(fp32, nrhs, width, per_wave, loc);
     if (!L.fn) return L;
-    L.ldx = pl.res_max_fp + (!loc && width > 14 ? 128 : 0);   // zeros at both ends, see resident.hip
+    L.ldx = pl.res_max_fp + (!loc && width > 14 ? 2 * kResPad : 0);   // zeros at both ends, see resident.hip
     if ((size_t)L.ldx * ts > 65536) return L;            // 16-bit byte offsets
     // LDS is handed out in pieces of 1280 bytes, which the occupancy query
     // does not count; every workgroup must be resident, so round up here

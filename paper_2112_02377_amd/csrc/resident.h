@@ -37,6 +37,15 @@ constexpr bool res_rhs_in_lds(size_t elem, int nrhs, int width, bool loc)
     return elem == 8 && nrhs == 1 && width > 14 && !loc;
 }
 
+// Entries of LDS kept at either end of the footprint where the wide
+// shift-table kernels read at row plus shift without a clamp.
+constexpr int32_t kResPad = 64;
+// Shift of a slot of a slice whose first row is row0: the table's, or for a
+// slice the tile does not have (a wave's second slice, past the tile's end)
+// the one that puts its 64 lanes on the first 64 entries -- its rows are
+// masked later, but every lane reads.
+constexpr int32_t res_wide_shift(bool live, int32_t table, int32_t row0) { return live ? table : -row0; }
+
 // Control words of one system, exchanged by its workgroups during a launch.
 // They are never reset: sweep k of a launch is written as kbase + k (modulo
 // 2^32), with a kbase beyond every sweep of the launches before, so what an

@@ -295,8 +295,9 @@ __device__ void res_decide(const ResParams& P, int32_t d, double* red)
 // SIMD, and with it tiles that fit the chip: there explicit positions sit in
 // LDS, four per 8 bytes, and a shift table takes one register per slice,
 // lane k holding slot k's shift (a lane read and an addition per slot; rows
-// without an entry of the shift reach at most 63 entries past either end of
-// the footprint, where zeros are kept).  Both slices of a wave are swept in
+// without an entry of the shift, and the lanes of a slice the tile does not
+// have, reach at most 63 entries past either end of the footprint, where
+// zeros are kept).  Both slices of a wave are swept in
 // one straight run of code, so their gathers and sums overlap: a workgroup
 // has about one wave per SIMD and nothing else hides LDS latency.  Slots past
 // a slice's width hold zeros and repeat the position of its last one.
@@ -327,7 +328,7 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
     const int32_t tid = threadIdx.x, lane = tid & 63;
     const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // LDS: x [buffers][NRHS][ldx], control words, gather offsets, positions, b
-    T* const lds_x = reinterpret_cast<T*>(smem) + (TABW ? 64 : 0);
+    T* const lds_x = reinterpret_cast<T*>(smem) + (TABW ? kResPad : 0);
     int32_t* const lds_ctl = reinterpret_cast<int32_t*>(smem + (DB ? 2 : 1) * res_x_bytes(ldx, NRHS, sizeof(T)));
     uint32_t* const lds_hg = reinterpret_cast<uint32_t*>(lds_ctl + kResCtlWords);
     uint2* const lds_pos = reinterpret_cast<uint2*>(lds_hg + (WIDE ? HU * kResBlock : 0));   // [group][row]
@@ -395,7 +396,8 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
                 if (k < w) a[j][k] = val[soff + (int64_t)k * 64 + lane];
             }
             if constexpr (TABW) {
-                shv[j] = w > 0 ? shift[(soff >> 6) + min(lane, w - 1)] * (int32_t)sizeof(T) : 0;
+                shv[j] = res_wide_shift(w > 0, w > 0 ? shift[(soff >> 6) + min(lane, w - 1)] : 0, r0 + (s - s0) * 64) *
+                         (int32_t)sizeof(T);
 #pragma unroll
                 for (int k = 0; k < W; ++k)
                     if (k < w && shift[(soff >> 6) + k] == own - r0 && a[j][k] != (T)0) d = a[j][k];
@@ -454,7 +456,7 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
     // stopped; then 1: gave up
     if (tid == 0) lds_ctl[kResGaveUp] = 0;
     if constexpr (TABW) {
-        if (tid < 64) {
+        if (tid < kResPad) {
 #pragma unroll
             for (int h = 0; h < (DB ? 2 : 1); ++h)
 #pragma unroll

@@ -1,0 +1,114 @@
+// Host-only checks of what the resident sweep loop takes from its plan (no
+// GPU).  Prints one summary line, or "FAIL ..." and exits 1.
+//
+// usage: resident_check positions N points mode nparts [sub]
+//   every LDS position the loop's kernels read for an N^3 grid's matrix of
+//   7-point or 27-point rows (27-point: a tenth of the edges dropped) under a
+//   split (mode 1 JB, 2 JBO, 3 JSS), lanes of absent rows and slices included
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <string>
+#include <vector>
+
+#include "jac_internal.h"
+#include "resident.h"
+
+namespace jac {
+void fail(jac_status s, const std::string& msg) { throw Error{s, msg}; }
+void hip_check(hipError_t, const char*) {}
+void set_last_error(const std::string&) {}
+}  // namespace jac
+
+using namespace jac;
+
+static int bad(const char* what, long long a, long long b)
+{
+    printf("FAIL %s %lld %lld\n", what, a, b);
+    return 1;
+}
+
+static Csr stencil(int N, int points)
+{
+    Csr a;
+    a.n = N * N * N;
+    a.rp.push_back(0);
+    for (int z = 0; z < N; ++z)
+        for (int y = 0; y < N; ++y)
+            for (int x = 0; x < N; ++x) {
+                for (int dz = -1; dz <= 1; ++dz)
+                    for (int dy = -1; dy <= 1; ++dy)
+                        for (int dx = -1; dx <= 1; ++dx) {
+                            const int u = x + dx, v = y + dy, w = z + dz;
+                            if (u < 0 || v < 0 || w < 0 || u >= N || v >= N || w >= N) continue;
+                            const int far = abs(dx) + abs(dy) + abs(dz);
+                            const int32_t r = x + N * (y + N * z), c = u + N * (v + N * w);
+                            if (points == 7 && far > 1) continue;
+                            // dropped for both rows of an edge alike
+                            if (far && points == 27 && ((uint32_t)(std::min(r, c) * 2654435761u + std::max(r, c) * 40503u) >> 7) % 10 == 0)
+                                continue;
+                            a.ci.push_back(c);
+                            a.v.push_back(far ? -1.0 : 30.0);
+                        }
+                a.rp.push_back((int32_t)a.ci.size());
+            }
+    return a;
+}
+
+static Plan plan_of(const Csr& a, int N, int mode, int P, int sg)
+{
+    const int32_t grid[3] = {N, N, N}, sub[3] = {sg, sg, sg};
+    Partition part = make_partition(a, mode, P, mode == JAC_SUBSTRUCT ? sub : nullptr, grid, 0);
+    std::vector<int64_t> src;
+    Csr pa = permute(a, part.perm, part.iperm, &src);
+    PlanParams prm;
+    prm.tile_rows = 512;
+    prm.lds_elems = 4096;
+    prm.staged = mode != JAC_BANDROW;
+    prm.fill_gap = mode == JAC_BANDROW_SP ? 16 : 0;
+    return make_plan(pa, part.cuts, prm);
+}
+
+static int positions(int argc, char** argv)
+{
+    const int N = atoi(argv[2]), points = atoi(argv[3]), mode = atoi(argv[4]), P = atoi(argv[5]);
+    const Plan pl = plan_of(stencil(N, points), N, mode, P, argc > 6 ? atoi(argv[6]) : 2);
+    const bool tabg = pl.colfmt == COL_TABG && !pl.res_run0.empty();
+    const bool wide = pl.max_width > 14 && pl.max_width <= kResWidth && pl.colfmt != COL_LOCAL16;
+    int64_t absent = 0, reads = 0;
+    if (wide && (tabg || pl.colfmt == COL_TABL)) {
+        const std::vector<int32_t>& shift = tabg ? pl.res_shift : pl.shift;
+        const std::vector<int32_t>& fps = tabg ? pl.res_fp : pl.tile_fp;
+        for (int32_t t = 0; t < pl.ntiles; ++t) {
+            const int32_t r0 = pl.tile_row0[t], s0 = pl.tile_slice0[t], s1 = pl.tile_slice0[t + 1];
+            for (int wave = 0; wave < kResBlock / 64; ++wave)
+                for (int j = 0; j < 2; ++j) {
+                    const int32_t s = s0 + wave + j * (kResBlock / 64);
+                    const bool live = s < s1;
+                    const int32_t w = live ? pl.slice_width[s] : 0;
+                    absent += !live;
+                    for (int k = 0; k < kResWidth; ++k) {
+                        const int32_t tab = w > 0 ? shift[(size_t)(pl.slice_off[s] / kSlice) + std::min(k, w - 1)] : 0;
+                        const int32_t sh = res_wide_shift(w > 0, tab, r0 + (s - s0) * kSlice);
+                        for (int lane = 0; lane < kSlice; ++lane, ++reads) {
+                            const int32_t pos = r0 + wave * 64 + lane + j * kResBlock + sh;
+                            if (pos < -kResPad || pos >= fps[t] + kResPad) return bad("position", t, pos);
+                        }
+                    }
+                }
+        }
+    }
+    printf("wide %d ntiles %d absent %lld reads %lld\n", wide ? 1 : 0, pl.ntiles, (long long)absent, (long long)reads);
+    return 0;
+}
+
+int main(int argc, char** argv)
+{
+    try {
+        if (argc >= 6 && !strcmp(argv[1], "positions")) return positions(argc, argv);
+    } catch (Error& e) {
+        printf("FAIL error %d %s\n", (int)e.status, e.msg.c_str());
+        return 1;
+    }
+    return 2;
+}
