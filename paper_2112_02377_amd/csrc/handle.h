@@ -11,6 +11,7 @@
 
 #include "jac_internal.h"
 #include "kernels.h"
+#include "resident.h"
 
 namespace jac {
 
@@ -86,8 +87,7 @@ struct Handle {
     int32_t grid[3] = {0, 0, 0};
     bool has_grid = false;
     bool planned = false;
-    uint32_t res_next = 0;         // resident launches: number of the next launch's first sweep
-    uint32_t res_arrived = 0;      // workgroups they have started
+    ResNumbers res_numbers;        // of the resident launches
     bool res_off = false;          // a resident launch gave up: per-sweep launches from then on
     Partition part;
     Plan plan;

@@ -83,6 +83,7 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     const int npart = res_partials(nrhs, width, loc);
     const size_t o_part = kResRingOff + up256((size_t)kResRing * vec);
     const size_t bytes = o_part + (size_t)kResPart * pl.ntiles * npart * nrhs * sizeof(double);
+    bool clear = h.res_numbers.restart();
     if (!d.res_work.p || d.res_work.bytes < bytes) {
         try {
             d.res_work.alloc(bytes);
@@ -91,10 +92,10 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
             (void)hipGetLastError();
             return L;                       // per-sweep launches need none of it
         }
-        launch_zero_u32(static_cast<uint32_t*>(d.res_work.p), (int32_t)(sizeof(ResCtl) / 4), h.stream);
-        h.res_next = kResPart;
-        h.res_arrived = 0;
+        h.res_numbers = ResNumbers();
+        clear = true;
     }
+    if (clear) launch_zero_u32(static_cast<uint32_t*>(d.res_work.p), (int32_t)(sizeof(ResCtl) / 4), h.stream);
     char* work = static_cast<char*>(d.res_work.p);
     ResSys& r = L.p.sys;
     r.tile_row0 = static_cast<const int32_t*>(pd.tile_row0.p);
@@ -132,8 +133,8 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
 // or gave up.
 bool res_run(Handle& h, ResLaunch& L, ResCtl& host, const void* from, void* to, bool fp32, int64_t m)
 {
-    L.p.kbase = h.res_next;
-    L.p.arrive = h.res_arrived + (uint32_t)L.grid;
+    L.p.kbase = h.res_numbers.next;
+    L.p.arrive = h.res_numbers.arrived + (uint32_t)L.grid;
     if (h.opt.timing) {
         for (auto& e : h.ev)
             if (!e) JAC_HIP(hipEventCreate(&e));
@@ -144,7 +145,7 @@ bool res_run(Handle& h, ResLaunch& L, ResCtl& host, const void* from, void* to, 
         h.res_off = true;
         return false;
     }
-    h.res_arrived = L.p.arrive;
+    h.res_numbers.arrived = L.p.arrive;
     if (h.opt.timing) JAC_HIP(hipEventRecord(h.ev[1], h.stream));
     if (to) launch_res_settle(fp32, h.stream, from, to, m, L.p.sys.ctl, L.p.kbase);
     JAC_HIP(hipMemcpyAsync(&host, L.p.sys.ctl, sizeof(ResCtl), hipMemcpyDeviceToHost, h.stream));
@@ -158,8 +159,7 @@ bool res_run(Handle& h, ResLaunch& L, ResCtl& host, const void* from, void* to, 
         JAC_HIP(hipEventElapsedTime(&ms, h.ev[0], h.ev[1]));
         h.last_loop_ms = ms;
     }
-    // no word of this launch lies beyond its last sweep by more than the tiles run ahead
-    h.res_next = L.p.kbase + (uint32_t)(L.p.solve ? host.last_k : L.p.kend) + 2 * kResPart;
+    h.res_numbers.passed(L.p.solve ? host.last_k : L.p.kend);
     return true;
 }
 

@@ -47,9 +47,10 @@ constexpr int32_t kResPad = 64;
 constexpr int32_t res_wide_shift(bool live, int32_t table, int32_t row0) { return live ? table : -row0; }
 
 // Control words of one system, exchanged by its workgroups during a launch.
-// They are never reset: sweep k of a launch is written as kbase + k (modulo
-// 2^32), with a kbase beyond every sweep of the launches before, so what an
-// earlier launch left reads as "not yet".
+// Sweep k of a launch is written as kbase + k, with a kbase beyond every
+// sweep of the launches before, so what an earlier launch left reads as "not
+// yet" and no launch has to reset them.  That holds for words less than 2^31
+// older than kbase: ResNumbers says when they are zeroed.
 struct ResCtl {
     uint32_t word[8];               // last sweep each deciding workgroup has decided
     uint32_t stop[4];               // column stopped on the residual of this sweep
@@ -60,6 +61,25 @@ struct ResCtl {
     int32_t last_k;                 // last sweep that stopped a column
     int32_t pad_;
     double nrm[4];                  // norm of the returned iterate per column
+};
+
+// The numbers a handle's launches give their sweeps and arrivals.
+struct ResNumbers {
+    static constexpr uint32_t kLimit = 1u << 30;
+    uint32_t next = kResPart;       // number of the next launch's first sweep; zeroed words are older
+    uint32_t arrived = 0;           // workgroups that all launches so far have started
+    // Before a launch: true when the control words have to be zeroed first
+    // (stop[] is written by solves alone, and fixed sweeps advance the
+    // numbers too).
+    bool restart()
+    {
+        if (next <= kLimit) return false;
+        *this = ResNumbers();
+        return true;
+    }
+    // After a launch whose last sweep was number `last`: the tiles ran ahead
+    // of it by less than kResPart sweeps.
+    void passed(int32_t last) { next += (uint32_t)last + 2 * kResPart; }
 };
 
 // One system of a resident launch (kernel argument).

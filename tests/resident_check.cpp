@@ -5,6 +5,9 @@
 //   every LDS position the loop's kernels read for an N^3 grid's matrix of
 //   7-point or 27-point rows (27-point: a tenth of the edges dropped) under a
 //   split (mode 1 JB, 2 JBO, 3 JSS), lanes of absent rows and slices included
+//    or: resident_check numbers sweeps
+//   what a solve left in the control words reads as "not yet" to every later
+//   launch, over launches of that many fixed sweeps whose numbers pass 2^32
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -102,9 +105,41 @@ static int positions(int argc, char** argv)
     return 0;
 }
 
+static int numbers(int32_t sweeps)
+{
+    ResNumbers nb;
+    ResCtl ctl{};
+    int64_t total = 0, launches = 0, clears = 0;
+    bool solve = true;
+    for (; total < (int64_t)5 << 31; ++launches) {
+        if (nb.restart()) {
+            ctl = ResCtl{};
+            ++clears;
+        }
+        const uint32_t kbase = nb.next;
+        for (int d = 0; d < kResDeciders; ++d)
+            if ((int32_t)(ctl.word[d] - kbase) >= 0) return bad("word", total, ctl.word[d]);
+        for (uint32_t w : ctl.stop)
+            if ((int32_t)(w - kbase) >= 0) return bad("stop word", total, w);
+        if (ctl.done == kbase || ctl.abort == kbase) return bad("done or abort", total, kbase);
+        const int32_t last = solve ? 5 : sweeps;
+        // the deciding workgroups' last words; stop words and done by solves alone
+        for (int d = 0; d < kResDeciders; ++d) ctl.word[d] = kbase + (uint32_t)last + kResDeciders - 1;
+        if (solve)
+            for (uint32_t& w : ctl.stop) w = kbase + 5;
+        if (solve) ctl.done = kbase;
+        solve = false;
+        nb.passed(last);
+        total += last;
+    }
+    printf("launches %lld clears %lld\n", (long long)launches, (long long)clears);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     try {
+        if (argc == 3 && !strcmp(argv[1], "numbers")) return numbers(atoi(argv[2]));
         if (argc >= 6 && !strcmp(argv[1], "positions")) return positions(argc, argv);
     } catch (Error& e) {
         printf("FAIL error %d %s\n", (int)e.status, e.msg.c_str());
