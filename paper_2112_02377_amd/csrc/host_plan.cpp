@@ -423,6 +423,19 @@ Plan make_plan(const Csr& a, const std::vector<int32_t>& cuts_in, const PlanPara
             pl.res_max_runs = std::max(pl.res_max_runs, nr);
         }
     }
+    if (tables && (prm.staged || !pl.res_shift.empty())) {
+        const std::vector<int32_t>& shift = prm.staged ? pl.shift : pl.res_shift;
+        for (int32_t t = 0; t < pl.ntiles; ++t) {
+            const int32_t fp = prm.staged ? pl.tile_fp[t] : pl.res_fp[t];
+            for (int32_t s = pl.tile_slice0[t]; s < pl.tile_slice0[t + 1]; ++s) {
+                const int32_t row0 = pl.slice_row0[s], last = std::min(pl.tile_row0[t + 1], row0 + kSlice) - 1;
+                for (int64_t k = pl.slice_off[s] / kSlice; k < pl.slice_off[s + 1] / kSlice; ++k) {
+                    pl.res_under = std::max(pl.res_under, -(row0 + shift[k]));
+                    pl.res_over = std::max(pl.res_over, last + shift[k] - (fp - 1));
+                }
+            }
+        }
+    }
     // a batch of slots may read up to 7 shifts past the last slice's last one
     if (tables) pl.shift.insert(pl.shift.end(), kSlice, 0);
     return pl;

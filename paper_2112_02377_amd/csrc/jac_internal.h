@@ -146,6 +146,9 @@ struct Plan {
     int32_t max_width = 0;            // slots of the widest slice
     int32_t max_tile_slices = 0;
     int32_t res_max_fp = 0, res_max_halo = 0, res_max_runs = 0;   // entries staged, entries of other tiles, runs
+    // shift tables: LDS positions that rows of a tile reach before and behind
+    // its footprint, through shifts that only other rows of their slice use
+    int32_t res_under = 0, res_over = 0;
 };
 
 Plan make_plan(const Csr& pa, const std::vector<int32_t>& cuts, const PlanParams& prm);

@@ -61,12 +61,14 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     // rows of more entries gathered than the width's kernel holds take the next wider one
     int width = pl.max_width;
     if (pl.res_max_halo > res_halo(width) * kResBlock) width = std::max(width, 8);
-    if (pl.res_max_halo > res_halo(width) * kResBlock) return L;
+    const bool wide = width > 14 && !loc;
+    const int32_t ends = wide ? pl.res_under + pl.res_over : 0;      // gathered with the entries of other tiles
+    if (pl.res_max_halo + ends > res_halo(width) * kResBlock) return L;
     const size_t ts = fp32 ? 4 : 8, vec = (size_t)h.a.n * nrhs * ts;
     if (vec >= ((size_t)1 << 32)) return L;              // 32-bit byte offsets into a ring slot
     L.fn = adjoint ? res_adjoint_kernel(width, per_wave) : res_kernel(fp32, nrhs, width, per_wave, loc);
     if (!L.fn) return L;
-    L.ldx = pl.res_max_fp + (!loc && width > 14 ? 2 * kResPad : 0);   // zeros at both ends, see resident.hip
+    L.ldx = pl.res_max_fp + (wide ? kResEnds : 1);       // and a zero for slots past a slice's width
     if ((size_t)L.ldx * ts > 65536) return L;            // 16-bit byte offsets
     // LDS is handed out in pieces of 1280 bytes, which the occupancy query
     // does not count; every workgroup must be resident, so round up here
@@ -123,6 +125,8 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     r.ctl = reinterpret_cast<ResCtl*>(work);
     r.n = h.a.n;
     r.ntiles = pl.ntiles;
+    r.under = wide ? pl.res_under : 0;
+    r.over = wide ? pl.res_over : 0;
     L.p.kend = kend;
     L.p.nd = kResDeciders;
     L.ok = true;

@@ -37,14 +37,29 @@ constexpr bool res_rhs_in_lds(size_t elem, int nrhs, int width, bool loc)
     return elem == 8 && nrhs == 1 && width > 14 && !loc;
 }
 
-// Entries of LDS kept at either end of the footprint where the wide
-// shift-table kernels read at row plus shift without a clamp.
+// A slot past a slice's width holds a zero value, and what x it multiplies
+// matters where x is infinite or NaN: as in the per-sweep launches, up to the
+// next multiple of their batch it is the slice's last slot's (FP64 sweeps;
+// the FP32 ones and the adjoint's steps stop at the width).  The slots beyond
+// read a zero.
+constexpr int res_padded(int w, bool batched) { return batched ? (w + 6) / 7 * 7 : w; }
+
+// The wide shift-table kernels read LDS at row plus shift without a clamp: up
+// to kResPad entries before the footprint hold its first entry, up to kResPad
+// behind it the last one (what the per-sweep launches' clamp reads for rows
+// without an entry of the shift), and kResPad zeros come before all.
 constexpr int32_t kResPad = 64;
-// Shift of a slot of a slice whose first row is row0: the table's, or for a
-// slice the tile does not have (a wave's second slice, past the tile's end)
-// the one that puts its 64 lanes on the first 64 entries -- its rows are
-// masked later, but every lane reads.
-constexpr int32_t res_wide_shift(bool live, int32_t table, int32_t row0) { return live ? table : -row0; }
+// Entries of LDS such a tile takes beside its footprint.
+constexpr int32_t kResEnds = 3 * kResPad;
+// Shift that puts the 64 lanes of a slice whose first row is row0 on the
+// zeros: slots past the width, and all slots of a slice the tile does not
+// have (a wave's second slice, past the tile's end).
+constexpr int32_t res_zero_shift(int32_t row0) { return -row0 - 2 * kResPad; }
+// Shift of slot k of a slice of w slots; last is the table's shift of slot min(k, w - 1).
+constexpr int32_t res_wide_shift(int k, int w, bool batched, int32_t last, int32_t row0)
+{
+    return k < res_padded(w, batched) ? last : res_zero_shift(row0);
+}
 
 // Control words of one system, exchanged by its workgroups during a launch.
 // Sweep k of a launch is written as kbase + k, with a kbase beyond every
@@ -103,6 +118,7 @@ struct ResSys {
     double* part;                   // [kResPart][ntiles][res_partials][nrhs]
     ResCtl* ctl;
     int32_t n, ntiles;
+    int32_t under, over;            // wide shift tables: entries read before and behind the footprint
     double thr[4];
     double big[4];
 };

@@ -295,12 +295,11 @@ __device__ void res_decide(const ResParams& P, int32_t d, double* red)
 // SIMD, and with it tiles that fit the chip: there explicit positions sit in
 // LDS, four per 8 bytes, and a shift table takes one register per slice,
 // lane k holding slot k's shift (a lane read and an addition per slot; rows
-// without an entry of the shift, and the lanes of a slice the tile does not
-// have, reach at most 63 entries past either end of the footprint, where
-// zeros are kept).  Both slices of a wave are swept in
+// without an entry of the shift reach at most 63 entries past either end of
+// the footprint, where copies of its first and last entry are kept).  Both slices of a wave are swept in
 // one straight run of code, so their gathers and sums overlap: a workgroup
 // has about one wave per SIMD and nothing else hides LDS latency.  Slots past
-// a slice's width hold zeros and repeat the position of its last one.
+// a slice's width hold zeros and read what res_padded says.
 //
 // ADJ: the reverse sweeps of the adjoint on the layout of A^T.  What is
 // exchanged is mu = D^{-1} lambda; lambda takes b's place (lambda -= A^T mu),
@@ -318,17 +317,22 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
     constexpr bool DB = res_two_buffers(NRHS, W, LOC);
     constexpr bool BL = res_rhs_in_lds(sizeof(T), NRHS, W, LOC);
     constexpr int NW = kResBlock / 64;
+    constexpr bool PAD = sizeof(T) == 8 && !ADJ;    // see res_padded
     const ResSys* const D = &P.sys;                 // kernel arguments
     const uint32_t kbase = P.kbase;
     const int32_t n = D->n;
     const int32_t r0 = ((cptr<const int32_t>)D->tile_row0)[tile], r1 = ((cptr<const int32_t>)D->tile_row0)[tile + 1];
     const int32_t s0 = ((cptr<const int32_t>)D->tile_slice0)[tile], s1 = ((cptr<const int32_t>)D->tile_slice0)[tile + 1];
-    const int32_t fp = ((cptr<const int32_t>)D->fp)[tile], own = ((cptr<const int32_t>)D->own)[tile];
-    const int32_t rows = r1 - r0, nh = fp - rows;
+    // positions count from the first entry a row reads (TABW: `under` entries before the footprint)
+    const int32_t under = TABW ? D->under : 0;
+    const int32_t fp = ((cptr<const int32_t>)D->fp)[tile] + under, own = ((cptr<const int32_t>)D->own)[tile] + under;
+    const int32_t rows = r1 - r0;
+    const int32_t nh = fp - rows + (TABW ? D->over : 0);   // entries to gather
     const int32_t tid = threadIdx.x, lane = tid & 63;
     const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // LDS: x [buffers][NRHS][ldx], control words, gather offsets, positions, b
-    T* const lds_x = reinterpret_cast<T*>(smem) + (TABW ? kResPad : 0);
+    T* const lds_zero = reinterpret_cast<T*>(smem);
+    T* const lds_x = lds_zero + (TABW ? 2 * kResPad - under : 1);
     int32_t* const lds_ctl = reinterpret_cast<int32_t*>(smem + (DB ? 2 : 1) * res_x_bytes(ldx, NRHS, sizeof(T)));
     uint32_t* const lds_hg = reinterpret_cast<uint32_t*>(lds_ctl + kResCtlWords);
     uint2* const lds_pos = reinterpret_cast<uint2*>(lds_hg + (WIDE ? HU * kResBlock : 0));   // [group][row]
@@ -353,7 +357,7 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
 #pragma unroll
         for (int u = 0; u < HU; ++u) {
             const int32_t e = min(u * kResBlock + tid, max(nh - 1, 0));
-            const int32_t pos = min(e < own ? e : e + rows, fp - 1);
+            const int32_t pos = min(max(e < own ? e : e + rows, under), fp - 1) - under;
             int32_t lo = 0, hi = nr - 1;
             while (lo < hi) {
                 const int32_t mid = (lo + hi + 1) >> 1;
@@ -396,11 +400,11 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
                 if (k < w) a[j][k] = val[soff + (int64_t)k * 64 + lane];
             }
             if constexpr (TABW) {
-                shv[j] = res_wide_shift(w > 0, w > 0 ? shift[(soff >> 6) + min(lane, w - 1)] : 0, r0 + (s - s0) * 64) *
-                         (int32_t)sizeof(T);
+                shv[j] = (res_wide_shift(lane, w, PAD, w > 0 ? shift[(soff >> 6) + min(lane, w - 1)] : 0,
+                                         r0 + (s - s0) * 64) + under) * (int32_t)sizeof(T);
 #pragma unroll
                 for (int k = 0; k < W; ++k)
-                    if (k < w && shift[(soff >> 6) + k] == own - r0 && a[j][k] != (T)0) d = a[j][k];
+                    if (k < w && shift[(soff >> 6) + k] == own - under - r0 && a[j][k] != (T)0) d = a[j][k];
             } else {
 #pragma unroll
                 for (int q = 0; q < NC; ++q) {
@@ -409,15 +413,15 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
                     for (int u = 0; u < 4; ++u) {
                         constexpr int kLast = W - 1;
                         const int k = min(4 * q + u, kLast);
-                        int32_t pos = 0;
-                        if (w > 0) {
+                        int32_t pos = -1;                           // a zero
+                        if (k < res_padded(w, PAD)) {
                             const int32_t kk = min(k, w - 1);
                             if constexpr (LOC) pos = col16[soff + (int64_t)kk * 64 + lane];
                             else pos = min(max(i + shift[(soff >> 6) + kk], 0), fp - 1);
                             // the row's diagonal: the slot of its own position
                             if (k < w && pos == own + (i - r0) && a[j][k] != (T)0) d = a[j][k];
                         }
-                        p4[u] = (uint32_t)pos * (uint32_t)sizeof(T);
+                        p4[u] = (uint32_t)(pos + 1) * (uint32_t)sizeof(T);
                     }
                     const uint2 p2 = make_uint2(p4[0] | p4[1] << 16, p4[2] | p4[3] << 16);
                     if constexpr (WIDE) lds_pos[q * (SPL * kResBlock) + j * kResBlock + tid] = p2;
@@ -455,16 +459,12 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
     // control words in LDS, by sweep parity: stop words, bit c: column c has
     // stopped; then 1: gave up
     if (tid == 0) lds_ctl[kResGaveUp] = 0;
-    if constexpr (TABW) {
-        if (tid < kResPad) {
+    // the zeros that slots past a slice's width read
+    if (tid < (TABW ? kResPad : 1)) {
 #pragma unroll
-            for (int h = 0; h < (DB ? 2 : 1); ++h)
+        for (int h = 0; h < (DB ? 2 : 1); ++h)
 #pragma unroll
-                for (int c = 0; c < NRHS; ++c) {
-                    lds_x[h * xbuf + c * ldx - 1 - tid] = (T)0;
-                    lds_x[h * xbuf + c * ldx + fp + tid] = (T)0;
-                }
-        }
+            for (int c = 0; c < NRHS; ++c) lds_zero[h * xbuf + c * ldx + tid] = (T)0;
     }
     __syncthreads();
 
@@ -579,6 +579,7 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
         asm volatile("" : "+v"(tv));
         int32_t* const lc = lds_ctl + (k & 1) * 8;
         const T* const xl = lds_x + (k & 1) * xbuf;
+        const T* const xg = TABW ? xl : xl - 1;     // what gathered positions count from
         if (tid == CT && P.solve) {
             int32_t any = 0;
 #pragma unroll
@@ -635,7 +636,7 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
 #pragma unroll
                             for (int c = 0; c < NRHS; ++c)
                                 x[u][c][j] =
-                                    *reinterpret_cast<const T*>(reinterpret_cast<const char*>(xl + c * ldx) + off);
+                                    *reinterpret_cast<const T*>(reinterpret_cast<const char*>(xg + c * ldx) + off);
                         }
                     }
             };
@@ -661,6 +662,9 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
                                 const T x = xv[b & 1][u][c][j], m = a[j0 + j][b * UB + u];
                                 if constexpr (sizeof(T) == 8) q[j0 + j][c] = __builtin_fma(m, x, q[j0 + j][c]);
                                 else q[j0 + j][c] = __builtin_fmaf(m, x, q[j0 + j][c]);
+                                // the per-sweep launches' batch ends one slot further
+                                if constexpr (PAD && W % 7 != 0)
+                                    if (b * UB + u == W - 1) q[j0 + j][c] = __builtin_fma((T)0, x, q[j0 + j][c]);
                             }
                     }
                 __builtin_amdgcn_sched_barrier(0);

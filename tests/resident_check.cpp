@@ -92,14 +92,22 @@ static int positions(int argc, char** argv)
                     absent += !live;
                     for (int k = 0; k < kResWidth; ++k) {
                         const int32_t tab = w > 0 ? shift[(size_t)(pl.slice_off[s] / kSlice) + std::min(k, w - 1)] : 0;
-                        const int32_t sh = res_wide_shift(w > 0, tab, r0 + (s - s0) * kSlice);
+                        const int32_t sh = res_wide_shift(k, w, true, tab, r0 + (s - s0) * kSlice);
                         for (int lane = 0; lane < kSlice; ++lane, ++reads) {
-                            const int32_t pos = r0 + wave * 64 + lane + j * kResBlock + sh;
-                            if (pos < -kResPad || pos >= fps[t] + kResPad) return bad("position", t, pos);
+                            const int32_t li = wave * 64 + lane + j * kResBlock, pos = r0 + li + sh;
+                            if (pos < -2 * kResPad || pos >= fps[t] + kResPad) return bad("position", t, pos);
+                            // zeros for slots past the padded width; else rows read entries that are there or copied
+                            if (k >= res_padded(w, true)) {
+                                if (pos >= -kResPad) return bad("zero position", t, pos);
+                            } else if (r0 + li < pl.tile_row0[t + 1] &&
+                                       (pos < -pl.res_under || pos >= fps[t] + pl.res_over)) {
+                                return bad("row's position", t, pos);
+                            }
                         }
                     }
                 }
         }
+        if (pl.res_under > kResPad || pl.res_over > kResPad) return bad("ends", pl.res_under, pl.res_over);
     }
     printf("wide %d ntiles %d absent %lld reads %lld\n", wide ? 1 : 0, pl.ntiles, (long long)absent, (long long)reads);
     return 0;

@@ -212,3 +212,74 @@ def test_adjoint_in_resident_launches(name, K, c):
     scale = np.abs(g).max()
     assert np.abs(out[1][0] - gbo).max() <= 1e-10 * scale and np.abs(out[1][1] - gvo).max() <= 1e-10 * scale
     assert rel_inf(out[1][2], xk) <= 1e-12
+
+
+def mixed_widths(n, halves, seed=8):
+    """Bands of changing width: row i reaches the columns within min(half_i, half_j)."""
+    rng = np.random.default_rng(seed)
+    half = np.repeat(halves, -(-n // len(halves)))[:n]
+    rows, cols = [], []
+    for i in range(n):
+        j = np.arange(max(0, i - half[i]), min(n, i + half[i] + 1))
+        j = j[np.abs(j - i) <= half[j]]
+        rows.append(np.full(len(j), i))
+        cols.append(j)
+    rows, cols = np.concatenate(rows), np.concatenate(cols)
+    v = np.where(rows == cols, 30.0, rng.uniform(-1.0, -0.1, len(rows)))
+    A = sp.csr_matrix((v, (rows, cols)), shape=(n, n))
+    A.sort_indices()
+    return W.CSRSystem(A.indptr.astype(np.int32), A.indices.astype(np.int32), A.data, rng.uniform(-1, 1, (1, n)))
+
+
+# slices as wide as the kernels' batches and narrower ones, in tables and in explicit columns; rows without some of
+# their slice's table entries at the ends of the footprint
+NONFINITE = {
+    "widths-7": (lambda: mixed_widths(1500, (3, 1, 2)), 1, 2, None, 1),
+    "widths-14": (lambda: mixed_widths(2100, (3, 6, 5)), 1, 2, None, 1),
+    "widths-27": (lambda: mixed_widths(2600, (3, 10, 13, 6, 8)), 1, 3, None, 1),
+    "widths-27-lists": (lambda: mixed_widths(2600, (3, 10, 13, 6, 8)), 2, 3, None, 2),
+    "bands": CASES["bands"],
+    "sub": CASES["sub"],
+    "fe-bands": CASES["fe-bands"],
+    "fe-lists": CASES["fe-lists"],
+    "fe-sub": CASES["fe-sub"],
+}
+
+
+@pytest.mark.parametrize("name", list(NONFINITE))
+def test_infinities_and_nans_spread_as_in_per_sweep_launches(name):
+    # a zero times an infinity is not a zero: what a padded slot multiplies
+    # decides which rows turn from infinite to NaN, and which stay finite
+    need_gpu()
+    b = B()
+    build, mode, P, sub, r = NONFINITE[name]
+    s = with_rhs(build(), r)
+    n = s.n
+    hs = [make(s, mode, P, sub, opts={b.JAC_OPT_GRID: g}) for g in (1, 0)]
+    rng = np.random.default_rng(12)
+    spots = [0, 1, 511, 512, n // 2, n - 64, n - 1] + list(rng.integers(0, n, 5))
+    for q, at in enumerate(int(a) for a in spots):
+        x0 = rng.uniform(-1, 1, (r, n))
+        x0[q % r, at] = (np.inf, -np.inf, np.nan)[q % 3]
+        out = []
+        for h in hs:
+            set_x(h, x0)
+            out.append((sweep(h, 9, r), get_x(h, n, r)))
+        info = b.jac_get_info(hs[1])
+        assert info["loop_grid"] == info["ntiles"] + 4
+        for u, v in zip(*out):
+            assert np.array_equal(u, v, equal_nan=True), (name, at, x0[q % r, at])
+        if r == 1:
+            g = rng.uniform(-1, 1, n)
+            g[at] = np.inf
+            out = []
+            for h in hs:
+                b.jac_set_x(h, None)
+                gb = torch.empty(n, dtype=torch.float64, device="cuda")
+                gv = torch.empty(s.nnz, dtype=torch.float64, device="cuda")
+                b.jac_adjoint(h, 10, 4, torch.from_numpy(g).cuda(), gb, gv)
+                out.append((gb.cpu().numpy(), gv.cpu().numpy()))
+            for u, v in zip(*out):
+                assert np.array_equal(u, v, equal_nan=True), (name, at, "adjoint")
+    for h in hs:
+        b.jac_destroy(h)
