@@ -126,7 +126,7 @@ typedef enum {
                                 column per slot, if that streams fewer bytes
                                 over the whole split; 0: never.  Results are
                                 bit-identical either way                       */
-    JAC_OPT_GRID = 13         /* 1 and 2 keep one launch per sweep.  Workgroups of
+    JAC_OPT_GRID = 13,        /* 1 and 2 keep one launch per sweep.  Workgroups of
                                 the one-launch-per-sweep loop of a
                                 single system (each of the eight XCDs sweeps a
                                 contiguous share of the tiles of about equal
@@ -139,6 +139,13 @@ typedef enum {
                                 the mean, counting streamed bytes and footprint
                                 runs), else 1.  Results are bit-identical
                                 either way (jac_info.loop_grid reports it)     */
+    JAC_OPT_LOOP_WAIT = 14    /* resident loop: microseconds a workgroup waits for
+                                another before the launch gives up (0: not at
+                                all) and the loop runs again as one launch per
+                                sweep, with the same results; default 2000000.
+                                The handle's next 32 loops (more after each
+                                further one that gives up) are launched per
+                                sweep                                          */
 } jac_option;
 
 typedef struct {
@@ -168,7 +175,9 @@ typedef struct {
     int32_t col_format;          /* 0 global int32 columns, 1 row-relative int16,
                                     2 tile-local uint16 (staged), 3 shift table,
                                     4 shift table into the staged footprint        */
-    int32_t pad2_;
+    int32_t resident_loops;      /* loops of this handle that ran as one resident
+                                    launch so far (sweeps, solves, the inner solves
+                                    of a refinement, reverse sweeps of an adjoint)  */
 } jac_info;
 
 /* Create a system from host CSR arrays (row_ptr[n+1], col_idx[nnz],

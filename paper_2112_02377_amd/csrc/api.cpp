@@ -905,6 +905,9 @@ jac_status jac_set_option(jac_handle h, jac_option opt, int64_t v)
         case JAC_OPT_TIMING:
             if (v != 0 && v != 1) fail(JAC_E_INVALID, "timing: 0 or 1");
             o.timing = (int32_t)v; break;
+        case JAC_OPT_LOOP_WAIT:
+            if (v < 0 || v > 20000000) fail(JAC_E_INVALID, "resident loop's wait in microseconds: 0..20000000");
+            o.loop_wait_us = (uint32_t)v; break;
         case JAC_OPT_PARTITIONER:
             if (v < 0 || v > 2) fail(JAC_E_INVALID, "partitioner: 0, 1 or 2");
             o.partitioner = (int32_t)v; break;
@@ -942,6 +945,7 @@ jac_status jac_get_option(jac_handle h, jac_option opt, int64_t* v)
         case JAC_OPT_CACHE: *v = o.cache; break;
         case JAC_OPT_SHIFT_TABLES: *v = o.tables; break;
         case JAC_OPT_GRID: *v = o.grid; break;
+        case JAC_OPT_LOOP_WAIT: *v = o.loop_wait_us; break;
         default: fail(JAC_E_INVALID, "unknown option");
         }
         return JAC_OK;
@@ -982,6 +986,7 @@ jac_status jac_get_info(jac_handle h, jac_info* info)
         i.keep_matrix = keep_matrix(h->opt.cache, h->stream_bytes(false));
         i.state_gen = h->state_gen;
         i.table_slots = h->plan.table_slots;
+        i.resident_loops = h->res_loops;
         *info = i;
         return JAC_OK;
     });

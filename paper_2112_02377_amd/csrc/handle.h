@@ -39,6 +39,7 @@ struct Options {
     int32_t inner_max = 256;
     int64_t ckpt_mb = 4096;
     int32_t timing = 0;
+    uint32_t loop_wait_us = 2000000;   // resident loop: longest wait for another workgroup
     int32_t partitioner = 0;
     int32_t cache = 0;         // matrix loads: 0 auto, 1 keep in cache, 2 stream (nontemporal)
     int32_t tables = 1;        // per-slice column shift tables where they stream fewer bytes
@@ -88,7 +89,8 @@ struct Handle {
     bool has_grid = false;
     bool planned = false;
     ResNumbers res_numbers;        // of the resident launches
-    bool res_off = false;          // a resident launch gave up: per-sweep launches from then on
+    ResRetry res_retry;            // after one that gave up
+    int32_t res_loops = 0;         // resident launches that ran to their end
     Partition part;
     Plan plan;
     Options opt;

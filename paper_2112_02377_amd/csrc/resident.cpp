@@ -52,7 +52,7 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     ResLaunch L;
     // Options that name a launch shape keep per-sweep launches (or the
     // persistent loop); the norm is summed in the order of 256 threads.
-    if (h.opt.loop != 0 || h.opt.grid != 0 || h.opt.block != kResBlock || kend < kResMinSweeps || h.res_off) return L;
+    if (h.opt.loop != 0 || h.opt.grid != 0 || h.opt.block != kResBlock || kend < kResMinSweeps) return L;
     const bool loc = pl.colfmt == COL_LOCAL16;
     const bool tabg = pl.colfmt == COL_TABG && !pl.res_run0.empty();
     if (!tabg && (adjoint || (!loc && pl.colfmt != COL_TABL))) return L;
@@ -80,6 +80,7 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     }
     L.grid = pl.ntiles + kResDeciders;
     if (L.grid > (int64_t)nb * num_cus()) return L;
+    if (!h.res_retry.now()) return L;
 
     DeviceArrays& d = h.d;
     const int npart = res_partials(nrhs, width, loc);
@@ -128,13 +129,14 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     r.under = wide ? pl.res_under : 0;
     r.over = wide ? pl.res_over : 0;
     L.p.kend = kend;
+    L.p.wait = h.opt.loop_wait_us * 100;
     L.p.nd = kResDeciders;
     L.ok = true;
     return L;
 }
 
-// Runs it and waits; false (and not tried again) if the launch was refused
-// or gave up.
+// Runs it and waits; false (and not tried again for a while) if the launch
+// was refused or gave up.
 bool res_run(Handle& h, ResLaunch& L, ResCtl& host, const void* from, void* to, bool fp32, int64_t m)
 {
     L.p.kbase = h.res_numbers.next;
@@ -146,7 +148,7 @@ bool res_run(Handle& h, ResLaunch& L, ResCtl& host, const void* from, void* to, 
     }
     if (launch_res(L.fn, L.grid, L.lds, L.ldx, h.stream, L.p) != hipSuccess) {
         (void)hipGetLastError();
-        h.res_off = true;
+        h.res_retry.failed();
         return false;
     }
     h.res_numbers.arrived = L.p.arrive;
@@ -155,9 +157,12 @@ bool res_run(Handle& h, ResLaunch& L, ResCtl& host, const void* from, void* to, 
     JAC_HIP(hipMemcpyAsync(&host, L.p.sys.ctl, sizeof(ResCtl), hipMemcpyDeviceToHost, h.stream));
     h.sync();
     if (host.abort == L.p.kbase) {
-        h.res_off = true;                   // do not wait that long again
+        h.res_numbers.passed(L.p.kend);
+        h.res_retry.failed();               // do not wait that long again soon
         return false;
     }
+    h.res_retry.ran();
+    ++h.res_loops;
     if (h.opt.timing) {
         float ms = 0.f;
         JAC_HIP(hipEventElapsedTime(&ms, h.ev[0], h.ev[1]));

@@ -97,6 +97,25 @@ struct ResNumbers {
     void passed(int32_t last) { next += (uint32_t)last + 2 * kResPart; }
 };
 
+// When a handle whose launch gave up or was refused tries again: after 32
+// loops as per-sweep launches, twice as many after each further failure, up
+// to 1024; at once after a success.
+struct ResRetry {
+    int32_t skip = 0, next = 32;
+    bool now()
+    {
+        if (skip == 0) return true;
+        --skip;
+        return false;
+    }
+    void failed()
+    {
+        skip = next;
+        next = next < 1024 ? 2 * next : 1024;
+    }
+    void ran() { next = 32; }
+};
+
 // One system of a resident launch (kernel argument).
 struct ResSys {
     const int32_t* tile_row0;
@@ -131,6 +150,7 @@ struct ResParams {
     void* xall;
     uint32_t kbase;                 // see ResCtl
     uint32_t arrive;                // ctl->arrived once every workgroup of this launch has arrived
+    uint32_t wait;                  // longest wait for another workgroup, in ticks of the 100 MHz clock
     int32_t nd;                     // deciding workgroups (1, 2, 4 or 8)
     int32_t kend, solve, norm_inf;
 };

@@ -34,8 +34,9 @@
 // words is device-coherent, none relies on what a kernel boundary does to the
 // caches) and waits once for all workgroups to have done so.
 //
-// Every wait is bounded by the clock; when one runs out all workgroups leave
-// and the host repeats the loop with a launch per sweep.
+// Every wait is bounded by the clock (2 s unless JAC_OPT_LOOP_WAIT says
+// otherwise); when one runs out all workgroups leave and the host repeats the
+// loop with a launch per sweep.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -51,7 +52,6 @@ namespace jac {
 namespace {
 
 constexpr int32_t kNever = kRunning;
-constexpr uint64_t kWaitTicks = 200000000ull;     // 2 s of the 100 MHz clock
 
 template <typename T> struct Bits;
 template <> struct Bits<double> {
@@ -101,16 +101,20 @@ __device__ __forceinline__ void lds_barrier()
 }
 
 // A bounded wait: true once it has run out or another workgroup gave up.
+// (Kernel arguments, read where they are needed; no wait at all: the first
+// value that is not there yet ends the launch.)
 struct Patience {
     uint64_t t0 = 0;
     uint32_t n = 0;
-    __device__ __forceinline__ bool out(ResCtl* ctl, uint32_t kbase)
+    __device__ __forceinline__ bool out(const ResParams& P)
     {
-        if ((++n & 63u) != 0) return false;
+        ResCtl* ctl = P.sys.ctl;
+        const uint32_t kbase = P.kbase;
+        if ((++n & 63u) != 0 && P.wait != 0) return false;
         const uint64_t t = wall_clock64();
         if (t0 == 0) t0 = t;
         if (ldc(&ctl->abort) == kbase) return true;
-        if (t - t0 > kWaitTicks) {
+        if (P.wait == 0 || t - t0 > P.wait) {
             stc(&ctl->abort, kbase);
             return true;
         }
@@ -130,7 +134,7 @@ __device__ __forceinline__ bool res_arrive(const ResParams& P, int32_t* ok)
         Patience wait;
         bool in = true;
         while ((int32_t)(ldc(&ctl->arrived) - P.arrive) < 0)
-            if (wait.out(ctl, P.kbase)) {
+            if (wait.out(P)) {
                 in = false;
                 break;
             }
@@ -186,7 +190,7 @@ __device__ void res_decide(const ResParams& P, int32_t d, double* red)
                     for (int q = 0; q < NP; ++q)
                         if (w[g][q] == B::sentinel) w[g][q] = ldc(&from[q]);
                 }
-                if (wait.out(ctl, kbase) || ((wait.n & 7u) == 0 && ldc(&ctl->done) == kbase)) {
+                if (wait.out(P) || ((wait.n & 7u) == 0 && ldc(&ctl->done) == kbase)) {
                     leave = true;
                     break;
                 }
@@ -237,7 +241,7 @@ __device__ void res_decide(const ResParams& P, int32_t d, double* red)
                 bool over = false;
                 for (int32_t j = max(0, k - P.nd + 1); j < k && !over; ++j)
                     while ((int32_t)(ldc(&ctl->word[j & (P.nd - 1)]) - kbase) < j) {
-                        over = ldc(&ctl->done) == kbase || w2.out(ctl, kbase);
+                        over = ldc(&ctl->done) == kbase || w2.out(P);
                         if (over) break;
                     }
                 if (over) stopped = (1u << NRHS) - 1u;
@@ -493,7 +497,7 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
 #pragma unroll
                 for (int c = 0; c < NRHS; ++c)
                     if (v[u][c] == SENT) v[u][c] = ldo(src + (int64_t)c * n, from(u, tv));
-            if (wait.out(ctl, kbase)) {
+            if (wait.out(P)) {
                 lds_ctl[kResGaveUp] = 1;
                 break;
             }
@@ -763,7 +767,7 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
                     for (;;) {
                         word = (int32_t)(ldc(&ctl->word[need & (nd - 1)]) - kbase);
                         if (word >= need || ldc(&ctl->done) == kbase) break;
-                        if (wait.out(ctl, kbase)) {
+                        if (wait.out(P)) {
                             lds_ctl[kResGaveUp] = 1;
                             break;
                         }
@@ -834,7 +838,7 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
     if (tid == 0) {
         Patience wait;
         while (ldc(&ctl->done) != kbase)
-            if (wait.out(ctl, kbase)) {
+            if (wait.out(P)) {
                 lds_ctl[kResGaveUp] = 1;
                 break;
             }

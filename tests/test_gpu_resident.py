@@ -283,3 +283,58 @@ def test_infinities_and_nans_spread_as_in_per_sweep_launches(name):
                 assert np.array_equal(u, v, equal_nan=True), (name, at, "adjoint")
     for h in hs:
         b.jac_destroy(h)
+
+
+@pytest.mark.parametrize("name", ["one-tile", "bands", "lists", "sub", "fe-bands", "fe-lists"])
+def test_a_launch_that_gives_up_is_repeated_per_sweep(name):
+    # no patience at all: the first value that is not there yet ends the
+    # launch in every workgroup, and each call starts over per sweep; 32
+    # loops later (64 after the next) the handle tries again
+    need_gpu()
+    b = B()
+    s, r, hs = pair(name)
+    h = hs[1]
+    x0 = np.random.default_rng(5).uniform(-1, 1, (r, s.n))
+    g = torch.from_numpy(np.random.default_rng(4).uniform(-1, 1, s.n)).cuda()
+    gb = torch.empty(s.n, dtype=torch.float64, device="cuda")
+    gv = torch.empty(s.nnz, dtype=torch.float64, device="cuda")
+
+    def fixed(h):
+        set_x(h, x0)
+        return [sweep(h, 37, r), get_x(h, s.n, r)]
+
+    def solve(h, prec=b.JAC_FP64, tol=1e-9):
+        b.jac_set_x(h, None)
+        st, sw, rr = b.jac_solve(h, tol, 20000, b.JAC_NORM_L2_REL, prec)
+        return [np.array(st), sw, rr, get_x(h, s.n, r)]
+
+    def refine(h):
+        return solve(h, b.JAC_FP32_REFINE, 1e-11)
+
+    def adjoint(h):
+        b.jac_adjoint(h, 30, 7, g, gb, gv)
+        return [gb.cpu().numpy(), gv.cpu().numpy(), get_x(h, s.n, r)]
+
+    for call in (fixed, solve, refine) + ((adjoint,) if r == 1 else ()):
+        want = call(hs[0])
+        ran = b.jac_get_info(h)["resident_loops"]
+        got = call(h)
+        assert b.jac_get_info(h)["resident_loops"] > ran, call.__name__        # the loop takes this call
+        ran = b.jac_get_info(h)["resident_loops"]
+        b.jac_set_option(h, b.JAC_OPT_LOOP_WAIT, 0)
+        gave_up = call(h)
+        b.jac_set_option(h, b.JAC_OPT_LOOP_WAIT, 2000000)
+        assert b.jac_get_info(h)["resident_loops"] == ran, call.__name__
+        for k, (u, v, w) in enumerate(zip(want, got, gave_up)):
+            assert np.array_equal(u, v) and np.array_equal(u, w), (name, call.__name__, k)
+        n = 0
+        while b.jac_get_info(h)["resident_loops"] == ran:                      # per sweep until it tries again
+            assert n < 80
+            b.jac_sweep(h, 8, None)
+            n += 1
+        got = call(h)
+        for k, (u, v) in enumerate(zip(want, got)):
+            assert np.array_equal(u, v), (name, call.__name__, k)
+    assert b.jac_get_info(hs[0])["resident_loops"] == 0
+    for h in hs:
+        b.jac_destroy(h)
