@@ -89,8 +89,7 @@ typedef enum {
                                 device at once, the tile, block and grid
                                 options leave it open and a call has eight
                                 sweeps or more: every sweep in one resident
-                                launch, the call then waits for it; else one
-                                launch per sweep.  Iterates, norms and stop
+                                launch; else one launch per sweep.  Iterates, norms and stop
                                 sweeps are the same bits.  1 = persistent
                                 cooperative loop with a grid barrier per sweep     */
     JAC_OPT_WG_PER_CU = 5,   /* persistent loop: workgroups per CU, default 2 (0 =
@@ -177,7 +176,8 @@ typedef struct {
                                     4 shift table into the staged footprint        */
     int32_t resident_loops;      /* loops of this handle that ran as one resident
                                     launch so far (sweeps, solves, the inner solves
-                                    of a refinement, reverse sweeps of an adjoint)  */
+                                    of a refinement, reverse sweeps of an adjoint;
+                                    of sweeps still running, not yet given up)      */
 } jac_info;
 
 /* Create a system from host CSR arrays (row_ptr[n+1], col_idx[nnz],

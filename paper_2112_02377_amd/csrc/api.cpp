@@ -986,6 +986,7 @@ jac_status jac_get_info(jac_handle h, jac_info* info)
         i.keep_matrix = keep_matrix(h->opt.cache, h->stream_bytes(false));
         i.state_gen = h->state_gen;
         i.table_slots = h->plan.table_slots;
+        h->res_poll();
         i.resident_loops = h->res_loops;
         *info = i;
         return JAC_OK;

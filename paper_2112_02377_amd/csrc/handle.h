@@ -73,9 +73,10 @@ struct DeviceArrays {
     DevMem t_map, a_gcol;
     DevMem adj_mu, adj_ck, adj_X, adj_M, adj_lam0, adj_lam1, adj_carry, adj_gb, adj_G, adj_sys, adj_segs, adj_fsegs;
     // resident loop: LDS layout of unstaged shift tables (the plan's res_
-    // arrays one after another), and one buffer for the ring of iterates,
-    // norm partials, descriptor and control words
-    DevMem res_plan, res_work;
+    // arrays one after another), one buffer for the ring of iterates, norm
+    // partials and control words, and the host's copy of what became of
+    // launches it does not wait for (pinned)
+    DevMem res_plan, res_work, res_seen;
     // asynchronous solve: descriptor, residual scratch, norms
     DevMem async_sys, async_r32, async_norm;
 };
@@ -90,7 +91,9 @@ struct Handle {
     bool planned = false;
     ResNumbers res_numbers;        // of the resident launches
     ResRetry res_retry;            // after one that gave up
-    int32_t res_loops = 0;         // resident launches that ran to their end
+    int32_t res_loops = 0;         // resident launches not known to have given up
+    uint32_t res_gave_up = 0;      // of the launches not waited for, those known to have given up
+    uint32_t res_open = 0;         // kbase of the last such launch, until it is known to have run
     Partition part;
     Plan plan;
     Options opt;
@@ -136,6 +139,7 @@ struct Handle {
     void require_plan() const;
     int lds_fp_bytes(bool fp32) const;
     int lds_tab() const;
+    void res_poll();               // takes note of resident launches that ended since the last call
 };
 
 int num_cus();
@@ -146,11 +150,12 @@ void run_loop(Handle& h, std::vector<SysDev>& sys, bool fp32, bool solve, int32_
               int fp_bytes, int runs, int colfmt, int nrhs, const std::vector<int64_t>* sys_bytes = nullptr);
 // The loop of one system in one resident launch (resident.cpp).  False, with
 // the starting iterate intact, when the split does not fit the chip, the
-// loop is too short or an option asks for per-sweep launches, or when the
-// launch gave up; the caller then runs run_loop.  Else the iterate is in
-// xout -- copied to x0_out when given -- and st holds the stop sweeps and
-// norms (solve mode).  xall: receives x_{k+1} at (k + 1) * n of every sweep
-// (fixed sweeps, one column).
+// loop is too short or an option asks for per-sweep launches; the caller then
+// runs run_loop.  Solves wait for the launch (false also when it gave up):
+// the iterate is in xout, copied to x0_out when given, st holds the stop
+// sweeps and norms.  Fixed sweeps (FP64) are only put on the stream, with
+// what does them again should the launch give up: x_K goes to x0_out, which
+// may be x0, and x_{k+1} of every sweep to (k + 1) * n of xall (one column).
 bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t kend, int norm_inf, double* hist,
                   const void* x0, void* xout, void* x0_out, SysState& st, double* xall = nullptr);
 // K reverse sweeps of the adjoint in one launch, on the plan of A^T: lam is

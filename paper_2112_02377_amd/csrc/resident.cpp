@@ -50,6 +50,7 @@ struct ResLaunch {
 ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp32, int nrhs, int32_t kend, bool adjoint)
 {
     ResLaunch L;
+    h.res_poll();
     // Options that name a launch shape keep per-sweep launches (or the
     // persistent loop); the norm is summed in the order of 256 threads.
     if (h.opt.loop != 0 || h.opt.grid != 0 || h.opt.block != kResBlock || kend < kResMinSweeps) return L;
@@ -135,9 +136,8 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     return L;
 }
 
-// Runs it and waits; false (and not tried again for a while) if the launch
-// was refused or gave up.
-bool res_run(Handle& h, ResLaunch& L, ResCtl& host, const void* from, void* to, bool fp32, int64_t m)
+// Puts it on the stream; false (and not tried again for a while) if it was refused.
+bool res_launch(Handle& h, ResLaunch& L)
 {
     L.p.kbase = h.res_numbers.next;
     L.p.arrive = h.res_numbers.arrived + (uint32_t)L.grid;
@@ -153,7 +153,21 @@ bool res_run(Handle& h, ResLaunch& L, ResCtl& host, const void* from, void* to, 
     }
     h.res_numbers.arrived = L.p.arrive;
     if (h.opt.timing) JAC_HIP(hipEventRecord(h.ev[1], h.stream));
-    if (to) launch_res_settle(fp32, h.stream, from, to, m, L.p.sys.ctl, L.p.kbase);
+    return true;
+}
+
+void res_time(Handle& h)
+{
+    if (!h.opt.timing) return;
+    JAC_HIP(hipEventSynchronize(h.ev[1]));
+    float ms = 0.f;
+    JAC_HIP(hipEventElapsedTime(&ms, h.ev[0], h.ev[1]));
+    h.last_loop_ms = ms;
+}
+
+// Waits for a launch and reads its result; false if it gave up.
+bool res_wait(Handle& h, const ResLaunch& L, ResCtl& host)
+{
     JAC_HIP(hipMemcpyAsync(&host, L.p.sys.ctl, sizeof(ResCtl), hipMemcpyDeviceToHost, h.stream));
     h.sync();
     if (host.abort == L.p.kbase) {
@@ -163,16 +177,28 @@ bool res_run(Handle& h, ResLaunch& L, ResCtl& host, const void* from, void* to, 
     }
     h.res_retry.ran();
     ++h.res_loops;
-    if (h.opt.timing) {
-        float ms = 0.f;
-        JAC_HIP(hipEventElapsedTime(&ms, h.ev[0], h.ev[1]));
-        h.last_loop_ms = ms;
-    }
+    res_time(h);
     h.res_numbers.passed(L.p.solve ? host.last_k : L.p.kend);
     return true;
 }
 
 }  // namespace
+
+void Handle::res_poll()
+{
+    const ResSeen* s = static_cast<const ResSeen*>(d.res_seen.p);
+    if (!s) return;
+    const uint32_t ended = __atomic_load_n(&s->ended, __ATOMIC_ACQUIRE);
+    const uint32_t failed = __atomic_load_n(&s->gave_up, __ATOMIC_RELAXED) - res_gave_up;
+    if (failed) {
+        res_gave_up += failed;
+        res_loops -= (int32_t)failed;
+        res_retry.failed();
+    } else if (res_open && ended == res_open) {
+        res_retry.ran();
+        res_open = 0;
+    }
+}
 
 bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t kend, int norm_inf, double* hist,
                   const void* x0, void* xout, void* x0_out, SysState& out, double* xall)
@@ -192,8 +218,28 @@ bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t ken
     L.p.xall = xall;
     L.p.solve = solve ? 1 : 0;
     L.p.norm_inf = norm_inf;
+    if (!solve) {
+        if (!h.d.res_seen.p) {
+            JAC_HIP(hipHostMalloc(&h.d.res_seen.p, sizeof(ResSeen), hipHostMallocDefault));
+            h.d.res_seen.bytes = sizeof(ResSeen);
+            h.d.res_seen.pinned = true;
+            *static_cast<ResSeen*>(h.d.res_seen.p) = ResSeen{};
+        }
+        if (!res_launch(h, L)) return false;
+        launch_res_finish(h.nrhs, h.plan.colfmt == COL_LOCAL16, h.plan.res_max_runs, h.stream, L.p,
+                          static_cast<double*>(x0_out), static_cast<ResSeen*>(h.d.res_seen.p));
+        h.res_numbers.passed(kend);
+        h.res_open = L.p.kbase;
+        ++h.res_loops;
+        res_time(h);
+        h.last_grid = L.grid;
+        h.last_loop_sweeps = kend;
+        return true;
+    }
+    if (!res_launch(h, L)) return false;
+    if (x0_out) launch_res_settle(fp32, h.stream, xout, x0_out, (int64_t)h.a.n * h.nrhs, r.ctl, L.p.kbase);
     ResCtl host;
-    if (!res_run(h, L, host, xout, x0_out, fp32, (int64_t)h.a.n * h.nrhs)) return false;
+    if (!res_wait(h, L, host)) return false;
     h.last_grid = L.grid;
     h.last_loop_sweeps = kend;
     for (int c = 0; c < 4; ++c) {
@@ -218,7 +264,7 @@ bool run_resident_adjoint(Handle& h, int32_t K, const double* lam, double* mu, d
     L.p.xall = mu;
     ResCtl host;
     const double ms = h.last_loop_ms;
-    const bool ok = res_run(h, L, host, nullptr, nullptr, false, 0);
+    const bool ok = res_launch(h, L) && res_wait(h, L, host);
     h.last_loop_ms = ms;                    // the forward's
     return ok;
 }

@@ -74,8 +74,16 @@ struct ResCtl {
     uint32_t arrived;               // workgroups that have cleared their share of the ring, all launches
     int32_t status;                 // JAC_OK, JAC_NOT_CONVERGED, JAC_E_DIVERGED
     int32_t last_k;                 // last sweep that stopped a column
-    int32_t pad_;
+    uint32_t redo_sweeps;           // fixed sweeps done again after a launch that gave up (see k_res_finish):
     double nrm[4];                  // norm of the returned iterate per column
+    uint64_t redo_next;             // ... the next (sweep, tile) to take, and those done
+    uint64_t redo_done;
+};
+
+// What the host learns of launches it does not wait for (pinned memory).
+struct ResSeen {
+    uint32_t ended;                 // kbase of the last launch that ended
+    uint32_t gave_up;               // launches that gave up
 };
 
 // The numbers a handle's launches give their sweeps and arrivals.
@@ -161,7 +169,11 @@ void* res_kernel(bool fp32, int nrhs, int width, int slices, bool explicit_cols)
 void* res_adjoint_kernel(int width, int slices);
 // ldx: x entries in LDS per right-hand side; lds: see res_lds in resident.cpp
 hipError_t launch_res(void* fn, int grid, size_t lds, int32_t ldx, hipStream_t st, ResParams p);
-// x0 = xout unless the launch gave up
+// After a launch of fixed FP64 sweeps: x0 = xout, or, if it gave up, its
+// sweeps again (loc: explicit LDS positions; runs: largest number of
+// footprint runs of a tile).
+void launch_res_finish(int nrhs, bool loc, int32_t runs, hipStream_t st, ResParams p, double* x0, ResSeen* seen);
+// After a solve: x0 = xout unless the launch gave up.
 void launch_res_settle(bool fp32, hipStream_t st, const void* xout, void* x0, int64_t m, const ResCtl* ctl,
                        uint32_t kbase);
 

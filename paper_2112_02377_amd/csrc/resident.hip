@@ -35,10 +35,13 @@
 // caches) and waits once for all workgroups to have done so.
 //
 // Every wait is bounded by the clock (2 s unless JAC_OPT_LOOP_WAIT says
-// otherwise); when one runs out all workgroups leave and the host repeats the
-// loop with a launch per sweep.
+// otherwise); when one runs out all workgroups leave and the loop is done
+// again: a solve or the adjoint by the host, with a launch per sweep; fixed
+// sweeps, which the host does not wait for, by the kernel that would have
+// copied their result.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <type_traits>
@@ -870,6 +873,9 @@ k_resident(ResParams P, int32_t ldx)
         if (wg == ntiles && threadIdx.x == 0) {
             stc(&P.sys.ctl->status, (int32_t)JAC_OK);
             stc(&P.sys.ctl->last_k, -1);
+            stc(&P.sys.ctl->redo_sweeps, 0u);
+            stc(&P.sys.ctl->redo_next, (uint64_t)0);
+            stc(&P.sys.ctl->redo_done, (uint64_t)0);
         }
         int32_t* ok = reinterpret_cast<int32_t*>(smem);
         if (!res_arrive(P, ok)) return;
@@ -880,6 +886,144 @@ k_resident(ResParams P, int32_t ldx)
     int32_t first, end, stride;
     xcd_items(ntiles, ntiles, wg, first, end, stride);
     res_tile<T, NRHS, W, SPL, LOC, ADJ>(P, first, smem, ldx);
+}
+
+// Closes a launch of fixed FP64 sweeps the host does not wait for: copies
+// x_K to its place and reports to the host, or, if the launch gave up, does
+// its sweeps again from x0, which is still intact: iterates, norms and kept
+// iterates to the bit, with nothing asked of the workgroups' residency.
+// Workgroups take (sweep, tile) items in order from a counter, and an item
+// waits for the end of the sweep before: every item it can wait for was taken
+// by a workgroup that is running, so each wait ends.  (x in two ring slots,
+// columns searched through the footprint's runs: some 60 us a sweep at 65^3
+// would do, and this one never has to be fast.)
+template <int NRHS>
+__global__ void __launch_bounds__(kResBlock) k_res_finish(ResParams P, int32_t loc, int32_t max_runs, double* x0_out,
+                                                          ResSeen* seen)
+{
+    extern __shared__ __align__(16) char smem[];
+    __shared__ double red[kResRed];
+    __shared__ uint64_t item_;
+    __shared__ int32_t last_;
+    const ResSys& S = P.sys;
+    ResCtl* ctl = S.ctl;
+    const int32_t n = S.n;
+    const bool gave_up = ldc(&ctl->abort) == P.kbase;
+    if (seen && blockIdx.x == 0 && threadIdx.x == 0) {
+        // host memory: plain loads and stores; launches of one stream, so one writer at a time
+        if (gave_up)
+            __hip_atomic_store(&seen->gave_up, __hip_atomic_load(&seen->gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&seen->ended, P.kbase, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    if (!gave_up) {
+        const int64_t m = (int64_t)n * NRHS;
+        for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
+            x0_out[i] = static_cast<const double*>(S.xout)[i];
+        return;
+    }
+    int32_t* lrl = reinterpret_cast<int32_t*>(smem);
+    int32_t* lrd = lrl + max_runs;
+    const int32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint64_t total = (uint64_t)P.kend * (uint64_t)S.ntiles;
+    const double* val = static_cast<const double*>(S.val);
+    const double* b = static_cast<const double*>(S.b);
+    const double* x0 = static_cast<const double*>(S.x0);
+    for (;;) {
+        if (tid == 0)
+            item_ = __hip_atomic_fetch_add(&ctl->redo_next, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        const uint64_t item = item_;
+        if (item >= total) return;
+        const int32_t k = (int32_t)(item / (uint64_t)S.ntiles), tile = (int32_t)(item % (uint64_t)S.ntiles);
+        if (tid == 0)
+            while (ldc(&ctl->redo_sweeps) < (uint32_t)k) __builtin_amdgcn_s_sleep(16);
+        const int32_t run0 = S.run0[tile], nr = S.run0[tile + 1] - run0;
+        for (int32_t q = tid; q < nr; q += kResBlock) {
+            lrl[q] = S.run_lds[run0 + q];
+            lrd[q] = S.run_delta[run0 + q];
+        }
+        __syncthreads();
+        const double* from = static_cast<const double*>(S.ring) + (int64_t)(k & 1) * n * NRHS;
+        double* to = static_cast<double*>(S.ring) + (int64_t)((k + 1) & 1) * n * NRHS;
+        auto x_at = [&](int32_t i, int c) -> double {
+            if (k == 0) return x0 ? x0[(int64_t)i * NRHS + c] : 0.0;
+            return ldc(&from[(int64_t)c * n + i]);
+        };
+        const int32_t r0 = S.tile_row0[tile], r1 = S.tile_row0[tile + 1];
+        const int32_t s0 = S.tile_slice0[tile], s1 = S.tile_slice0[tile + 1];
+        const int32_t fp = S.fp[tile], own = S.own[tile];
+        double acc[NRHS];
+#pragma unroll
+        for (int c = 0; c < NRHS; ++c) acc[c] = 0.0;
+        for (int32_t s = s0 + wave; s < s1; s += kResBlock / 64) {
+            const int64_t soff = S.slice_off[s];
+            const int32_t w = (int32_t)((S.slice_off[s + 1] - soff) >> 6);
+            const int32_t i = r0 + (s - s0) * 64 + lane;
+            if (i >= r1) continue;
+            double q[NRHS], d = 1.0;
+#pragma unroll
+            for (int c = 0; c < NRHS; ++c) q[c] = 0.0;
+            for (int32_t e = 0; e < res_padded(w, true); ++e) {
+                const int32_t ee = min(e, w - 1);
+                const int64_t slot = soff + (int64_t)ee * 64 + lane;
+                const double a = e < w ? val[slot] : 0.0;
+                const int32_t pos = loc ? (int32_t)S.col16[slot] : min(max(i + S.shift[(soff >> 6) + ee], 0), fp - 1);
+                const bool diag = loc ? pos == own + (i - r0) : S.shift[(soff >> 6) + ee] == own - r0;
+                int32_t lo = 0, hi = nr - 1;
+                while (lo < hi) {
+                    const int32_t mid = (lo + hi + 1) >> 1;
+                    if (lrl[mid] <= pos) lo = mid; else hi = mid - 1;
+                }
+                const int32_t col = pos + lrd[lo];
+#pragma unroll
+                for (int c = 0; c < NRHS; ++c) q[c] = __builtin_fma(a, x_at(col, c), q[c]);
+                if (diag && a != 0.0) d = a;
+            }
+            const double di = 1.0 / d;
+#pragma unroll
+            for (int c = 0; c < NRHS; ++c) {
+                const double r = b[(int64_t)i * NRHS + c] - q[c];
+                const double x = __builtin_fma(di, r, x_at(i, c));
+                stc(&to[(int64_t)c * n + i], x);
+                if (k + 1 == P.kend) x0_out[(int64_t)i * NRHS + c] = x;
+                if (NRHS == 1 && P.xall) static_cast<double*>(P.xall)[(int64_t)(k + 1) * n + i] = x;
+                acc[c] = __builtin_fma(r, r, acc[c]);
+            }
+        }
+        wait_own();
+        block_reduce<NRHS>(acc, false, red);        // its barriers: every wave's stores have reached the device
+        double* part = S.part + (int64_t)(k & 1) * S.ntiles * NRHS;
+        if (tid == 0) {
+#pragma unroll
+            for (int c = 0; c < NRHS; ++c) stc(&part[(int64_t)tile * NRHS + c], acc[c]);
+            wait_own();
+            last_ = (__hip_atomic_fetch_add(&ctl->redo_done, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1) %
+                        (uint64_t)S.ntiles == 0;
+        }
+        __syncthreads();
+        if (last_) {
+            // the sweep's last tile: its norm, in the order of the other loops, before the next sweep starts
+            double v[NRHS];
+#pragma unroll
+            for (int c = 0; c < NRHS; ++c) v[c] = 0.0;
+            for (int32_t t = tid; t < S.ntiles; t += kResBlock)
+#pragma unroll
+                for (int c = 0; c < NRHS; ++c) v[c] = v[c] + ldc(&part[(int64_t)t * NRHS + c]);
+            block_reduce<NRHS>(v, false, red);
+            if (tid == 0) {
+#pragma unroll
+                for (int c = 0; c < NRHS; ++c)
+                    if (P.hist) P.hist[(int64_t)k * NRHS + c] = sqrt(v[c]);
+                stc(&ctl->redo_sweeps, (uint32_t)k + 1);
+            }
+        }
+        // Thread 0's branch above and its claim of the next item must not meet
+        // across the loop's end: the compiler then threads one into the other
+        // and sends the other threads round a loop of their own, past the
+        // barrier, on the old item.
+        __syncthreads();
+    }
 }
 
 template <typename U>
@@ -939,6 +1083,17 @@ hipError_t launch_res(void* fn, int grid, size_t lds, int32_t ldx, hipStream_t s
 {
     void* args[] = {&p, &ldx};
     return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(kResBlock), args, (unsigned)lds, st);
+}
+
+void launch_res_finish(int nrhs, bool loc, int32_t runs, hipStream_t st, ResParams p, double* x0, ResSeen* seen)
+{
+    const int64_t m = (int64_t)p.sys.n * nrhs;
+    const int g = (int)std::min<int64_t>((m + kResBlock - 1) / kResBlock, 2048);
+    const size_t lds = (size_t)runs * 8;
+    if (nrhs == 1) k_res_finish<1><<<g, kResBlock, lds, st>>>(p, loc, runs, x0, seen);
+    else if (nrhs == 2) k_res_finish<2><<<g, kResBlock, lds, st>>>(p, loc, runs, x0, seen);
+    else k_res_finish<4><<<g, kResBlock, lds, st>>>(p, loc, runs, x0, seen);
+    JAC_HIP(hipGetLastError());
 }
 
 void launch_res_settle(bool fp32, hipStream_t st, const void* xout, void* x0, int64_t m, const ResCtl* ctl,

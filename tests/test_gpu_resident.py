@@ -338,3 +338,66 @@ def test_a_launch_that_gives_up_is_repeated_per_sweep(name):
     assert b.jac_get_info(hs[0])["resident_loops"] == 0
     for h in hs:
         b.jac_destroy(h)
+
+
+def busy_stream(ms):
+    """Puts about `ms` of device work on the current stream and returns an event behind it."""
+    torch.cuda._sleep(int(ms * 1e-3 * 1.0e8))                     # ticks of the device's 100 MHz clock
+    e = torch.cuda.Event()
+    e.record()
+    return e
+
+
+def test_fixed_sweeps_do_not_wait_for_the_device():
+    # jac_sweep and jac_sweep_checkpointed return with their work on the stream, also in a resident launch
+    need_gpu()
+    b = B()
+    s = W.laplace7(20, workload=1)
+    h = make(s, 1, 2)
+    hist = torch.zeros(50, dtype=torch.float64, device="cuda")
+    x = torch.empty(s.n, dtype=torch.float64, device="cuda")
+    b.jac_sweep(h, 50, hist)                                      # first calls allocate, which waits
+    b.jac_sweep_checkpointed(h, 50, 10)
+    torch.cuda.synchronize()
+    b.jac_set_x(h, None)
+    before = busy_stream(500)
+    b.jac_sweep(h, 50, hist)
+    b.jac_get_x(h, x)
+    assert not before.query()
+    torch.cuda.synchronize()
+    b.jac_set_x(h, None)
+    before = busy_stream(500)
+    b.jac_sweep_checkpointed(h, 50, 10)
+    assert not before.query()
+    torch.cuda.synchronize()
+    assert b.jac_get_info(h)["resident_loops"] == 4
+    _, xr, hr = ref.sweeps(s.row_ptr, s.col_idx, s.vals, s.b[0], 50)
+    assert rel_inf(x.cpu().numpy(), xr) <= 1e-12 and rel_inf(get_x(h, s.n)[0], xr) <= 1e-12
+    assert np.all(np.abs(hist.cpu().numpy() - hr) <= 1e-12 * np.maximum(hr, hr[0] * 1e-3))
+    b.jac_destroy(h)
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_fixed_sweeps_of_launches_that_give_up_are_done_again_on_the_device(name):
+    # several on the stream before the host can know, infinities among x
+    need_gpu()
+    b = B()
+    s, r, hs = pair(name)
+    x0 = np.random.default_rng(5).uniform(-1, 1, (r, s.n))
+    x0[0, s.n // 2] = np.inf
+    b.jac_set_option(hs[1], b.JAC_OPT_LOOP_WAIT, 0)
+    out = []
+    for h in hs:
+        set_x(h, x0)
+        hist = [torch.zeros(K * r, dtype=torch.float64, device="cuda") for K in (8, 21)]
+        for hi in hist:
+            b.jac_sweep(h, hi.numel() // r, hi)
+        x = torch.empty(s.n * r, dtype=torch.float64, device="cuda")
+        b.jac_get_x(h, x)
+        torch.cuda.synchronize()
+        out.append([t.cpu().numpy() for t in hist + [x]])
+    assert b.jac_get_info(hs[1])["resident_loops"] == 0
+    for k, (u, v) in enumerate(zip(*out)):
+        assert np.array_equal(u, v, equal_nan=True), (name, k)
+    for h in hs:
+        b.jac_destroy(h)
