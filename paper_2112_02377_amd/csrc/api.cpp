@@ -567,6 +567,10 @@ jac_status jac_create(int32_t n, const int32_t* row_ptr, const int32_t* col_idx,
         h->stream = static_cast<hipStream_t>(hip_stream);
         JAC_HIP(hipGetDevice(&h->device));
         h->d.bad.alloc(sizeof(int32_t));
+        JAC_HIP(hipHostMalloc(&h->d.res_seen.p, sizeof(ResSeen), hipHostMallocDefault));
+        h->d.res_seen.bytes = sizeof(ResSeen);
+        h->d.res_seen.pinned = true;
+        *static_cast<ResSeen*>(h->d.res_seen.p) = ResSeen{};
         h->d.vals_caller.alloc((size_t)h->a.nnz() * sizeof(double));
         if (h->a.nnz())
             JAC_HIP(hipMemcpyAsync(h->d.vals_caller.p, h->a.v.data(), (size_t)h->a.nnz() * sizeof(double),

@@ -187,7 +187,6 @@ bool res_wait(Handle& h, const ResLaunch& L, ResCtl& host)
 void Handle::res_poll()
 {
     const ResSeen* s = static_cast<const ResSeen*>(d.res_seen.p);
-    if (!s) return;
     const uint32_t ended = __atomic_load_n(&s->ended, __ATOMIC_ACQUIRE);
     const uint32_t failed = __atomic_load_n(&s->gave_up, __ATOMIC_RELAXED) - res_gave_up;
     if (failed) {
@@ -219,12 +218,6 @@ bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t ken
     L.p.solve = solve ? 1 : 0;
     L.p.norm_inf = norm_inf;
     if (!solve) {
-        if (!h.d.res_seen.p) {
-            JAC_HIP(hipHostMalloc(&h.d.res_seen.p, sizeof(ResSeen), hipHostMallocDefault));
-            h.d.res_seen.bytes = sizeof(ResSeen);
-            h.d.res_seen.pinned = true;
-            *static_cast<ResSeen*>(h.d.res_seen.p) = ResSeen{};
-        }
         if (!res_launch(h, L)) return false;
         launch_res_finish(h.nrhs, h.plan.colfmt == COL_LOCAL16, h.plan.res_max_runs, h.stream, L.p,
                           static_cast<double*>(x0_out), static_cast<ResSeen*>(h.d.res_seen.p));
