@@ -164,9 +164,9 @@ static void forward_ckpt(Handle& h, int32_t K, int32_t c)
     h.ckpt_K = -1;
     if (all) {
         auto CK = [&](int j) { return static_cast<double*>(d.adj_ck.p) + (size_t)j * n; };
-        SysState none;
         launch_gather_in(nullptr, static_cast<const int32_t*>(d.perm.p), n, 1, CK(0), st);
-        if (run_resident(h, sA, false, false, K, 0, nullptr, nullptr, d.x1.p, d.x0.p, none, CK(0))) {
+        const int32_t done = run_resident_sweeps(h, sA, K, nullptr, nullptr, d.x1.p, d.x0.p, CK(0));
+        if (K > 0 && done == K) {
             h.ckpt_K = K;
             h.ckpt_c = c;
             h.ckpt_all = true;
@@ -188,7 +188,7 @@ static void forward_ckpt(Handle& h, int32_t K, int32_t c)
         const size_t lds = loop_lds_bytes(fpb, tab, 0);
         const int grid = sweep_grid(h, fn, h.opt.block, lds);
         launch_init_state(static_cast<SysState*>(d.state.p), 1, st);
-        for (int32_t k = 0; k < K; ++k) {
+        for (int32_t k = done; k < K; ++k) {
             // sweep 0 of its own descriptor: reads x[0], writes x[1], decides nothing
             LoopParams p{};
             p.sys = static_cast<const SysDev*>(d.adj_fsegs.p) + k;

@@ -744,9 +744,10 @@ jac_status jac_sweep(jac_handle h, int32_t nsweeps, double* hist_dev)
         if (nsweeps == 0) return JAC_OK;
         ++h->state_gen;
         std::vector<SysDev> sys = {h->sysdev(false)};
-        SysState st;
-        if (run_resident(*h, sys[0], false, false, nsweeps, 0, hist_dev, h->d.x0.p, h->d.x1.p, h->d.x0.p, st))
-            return JAC_OK;
+        const int32_t done = run_resident_sweeps(*h, sys[0], nsweeps, hist_dev, h->d.x0.p, h->d.x1.p, h->d.x0.p);
+        if (done == nsweeps) return JAC_OK;
+        nsweeps -= done;
+        if (hist_dev) hist_dev += (int64_t)done * h->nrhs;
         std::vector<int32_t> tb = {0, h->plan.ntiles};
         run_loop(*h, sys, false, false, nsweeps, 0, hist_dev, h->d.sys, h->d.state, h->d.tile_base, tb,
                  h->lds_fp_bytes(false), h->lds_tab(), h->plan.colfmt, h->nrhs);
@@ -771,7 +772,7 @@ static jac_status solve64(Handle& h, double tol, int32_t maxit, int norm, int32_
     SysState st;
     const int norm_inf = norm == JAC_NORM_INF_ABS ? 1 : 0;
     const bool resident =
-        run_resident(h, s, false, true, maxit, norm_inf, nullptr, h.d.x0.p, h.d.x1.p, h.d.x0.p, st);
+        run_resident_solve(h, s, false, maxit, norm_inf, h.d.x0.p, h.d.x0.p, h.d.x1.p, h.d.x2.p, st);
     if (!resident) {
         std::vector<SysDev> sys = {s};
         std::vector<int32_t> tb = {0, h.plan.ntiles};

@@ -148,16 +148,22 @@ int sweep_grid(const Handle& h, void* fn, int block, size_t lds);
 void run_loop(Handle& h, std::vector<SysDev>& sys, bool fp32, bool solve, int32_t kend, int norm_inf, double* hist,
               DevMem& d_sys, DevMem& d_state, DevMem& d_tile_base, const std::vector<int32_t>& tile_base,
               int fp_bytes, int runs, int colfmt, int nrhs, const std::vector<int64_t>* sys_bytes = nullptr);
-// The loop of one system in one resident launch (resident.cpp).  False, with
-// the starting iterate intact, when the split does not fit the chip, the
-// loop is too short or an option asks for per-sweep launches; the caller then
-// runs run_loop.  Solves wait for the launch (false also when it gave up):
-// the iterate is in xout, copied to x0_out when given, st holds the stop
-// sweeps and norms.  Fixed sweeps (FP64) are only put on the stream, with
-// what does them again should the launch give up: x_K goes to x0_out, which
-// may be x0, and x_{k+1} of every sweep to (k + 1) * n of xall (one column).
-bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t kend, int norm_inf, double* hist,
-                  const void* x0, void* xout, void* x0_out, SysState& st, double* xall = nullptr);
+// The loop of one system in resident launches (resident.cpp), which take it
+// unless the split does not fit the chip, the loop is too short or an option
+// asks for per-sweep launches.
+//
+// Fixed FP64 sweeps from x0 (null: zero) are only put on the stream, with
+// what does them again should a launch give up; the number of them, K but for
+// a launch that was refused.  x_K of those goes to x0_out, which may be x0
+// (xout: a vector to work in), and x_{k+1} of every sweep to (k + 1) * n of
+// xall (one column).
+int32_t run_resident_sweeps(Handle& h, const SysDev& s, int32_t K, double* hist, const void* x0, void* xout, void* x0_out,
+                            double* xall = nullptr);
+// A solve waits for its launches: false, with x0 intact, also when one gave
+// up.  Else the iterate is in x0_out, which may be x0, and st holds the stop
+// sweeps and norms; xa and xb: vectors to work in.
+bool run_resident_solve(Handle& h, const SysDev& s, bool fp32, int32_t maxit, int norm_inf, const void* x0, void* x0_out,
+                        void* xa, void* xb, SysState& st);
 // K reverse sweeps of the adjoint in one launch, on the plan of A^T: lam is
 // lambda_K, mu receives mu_k at (k - 1) * n for k = 1 .. K, gb their sum.
 bool run_resident_adjoint(Handle& h, int32_t K, const double* lam, double* mu, double* gb);

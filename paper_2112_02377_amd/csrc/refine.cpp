@@ -116,7 +116,7 @@ jac_status solve_refine(Handle& h, double tol, int32_t maxit, int norm, int32_t*
         budget = std::max(budget, 1);
         SysState st;
         const bool resident =
-            run_resident(h, s32, true, true, budget, norm_inf, nullptr, nullptr, h.d.d0.p, nullptr, st);
+            run_resident_solve(h, s32, true, budget, norm_inf, nullptr, h.d.d0.p, h.d.d1.p, h.d.d2.p, st);
         if (!resident) {
             JAC_HIP(hipMemsetAsync(h.d.d0.p, 0, fbytes, h.stream));
             std::vector<SysDev> sys = {s32};

@@ -1,6 +1,7 @@
 // Host side of the resident loop: which loops take it, its buffers, launch
 // and result.
 #include <algorithm>
+#include <limits>
 
 #include "handle.h"
 #include "launch.h"
@@ -14,11 +15,19 @@ namespace {
 // takes about 20 us from queue to queue, a per-sweep launch of a small
 // system 5.4 us against 1.5-2.5 us for a resident sweep.
 constexpr int32_t kResMinSweeps = 8;
+// Sweeps of one launch at most: it occupies its compute units until it ends
+// (65536 sweeps are 0.15 to 0.35 s), where other streams' work got its turn
+// between per-sweep launches.  Longer loops are several launches; one more
+// costs about 20 us.
+constexpr int32_t kResMaxSweeps = 1 << 16;
 
 // The ring starts on a boundary of its own, clear of the control words (its
 // distance from them made no difference: 64 KiB, 320 KiB and 2 MiB measured).
 constexpr size_t kResRingOff = 65536;
 static_assert(sizeof(ResCtl) <= kResRingOff, "control words");
+
+// Launches of a loop, of about equal length (none of several below half the most).
+int32_t res_launches(int32_t sweeps) { return (int32_t)(((int64_t)sweeps + kResMaxSweeps - 1) / kResMaxSweeps); }
 
 size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
@@ -53,7 +62,7 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     h.res_poll();
     // Options that name a launch shape keep per-sweep launches (or the
     // persistent loop); the norm is summed in the order of 256 threads.
-    if (h.opt.loop != 0 || h.opt.grid != 0 || h.opt.block != kResBlock || kend < kResMinSweeps) return L;
+    if (h.opt.loop != 0 || h.opt.grid != 0 || h.opt.block != kResBlock || kend < kResMinSweeps || kend > kResMaxSweeps) return L;
     const bool loc = pl.colfmt == COL_LOCAL16;
     const bool tabg = pl.colfmt == COL_TABG && !pl.res_run0.empty();
     if (!tabg && (adjoint || (!loc && pl.colfmt != COL_TABL))) return L;
@@ -199,8 +208,55 @@ void Handle::res_poll()
     }
 }
 
-bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t kend, int norm_inf, double* hist,
-                  const void* x0, void* xout, void* x0_out, SysState& out, double* xall)
+// Fixed FP64 sweeps of one launch, x_0 in x0 (null: zero), x_K to x0_out.
+static bool res_sweeps(Handle& h, const SysDev& s, int32_t kend, double* hist, const void* x0, void* xout, void* x0_out,
+                       double* xall)
+{
+    ResLaunch L = res_prepare(h, h.plan, h.d, false, h.nrhs, kend, false);
+    if (!L.ok) return false;
+    ResSys& r = L.p.sys;
+    r.val = s.val;
+    r.b = s.b;
+    r.x0 = x0;
+    r.xout = xout;
+    L.p.hist = hist;
+    L.p.xall = xall;
+    if (!res_launch(h, L)) return false;
+    launch_res_finish(h.nrhs, h.plan.colfmt == COL_LOCAL16, h.plan.res_max_runs, h.stream, L.p,
+                      static_cast<double*>(x0_out), static_cast<ResSeen*>(h.d.res_seen.p));
+    h.res_numbers.passed(kend);
+    h.res_open = L.p.kbase;
+    ++h.res_loops;
+    res_time(h);
+    h.last_grid = L.grid;
+    return true;
+}
+
+int32_t run_resident_sweeps(Handle& h, const SysDev& s, int32_t K, double* hist, const void* x0, void* xout, void* x0_out,
+                            double* xall)
+{
+    const int32_t launches = res_launches(K);
+    double ms = 0.0;
+    int32_t done = 0;
+    for (int32_t q = 0; q < launches; ++q) {
+        const int32_t k1 = (int32_t)((int64_t)K * (q + 1) / launches);
+        if (!res_sweeps(h, s, k1 - done, hist ? hist + (int64_t)done * h.nrhs : nullptr, q == 0 ? x0 : x0_out, xout,
+                        x0_out, xall ? xall + (int64_t)done * h.a.n : nullptr))
+            break;
+        done = k1;
+        ms += h.last_loop_ms;
+    }
+    if (done) {
+        h.last_loop_sweeps = done;
+        if (h.opt.timing) h.last_loop_ms = ms;
+    }
+    return done;
+}
+
+// One launch of a solve; false also when it gave up.  x0_out (null: not
+// wanted) receives the iterate, unless more sweeps follow and a column needs them.
+static bool res_solve(Handle& h, const SysDev& s, bool fp32, int32_t kend, int norm_inf, const void* x0, void* xout,
+                      void* x0_out, bool more, SysState& out)
 {
     ResLaunch L = res_prepare(h, h.plan, h.d, fp32, h.nrhs, kend, false);
     if (!L.ok) return false;
@@ -213,28 +269,14 @@ bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t ken
         r.thr[c] = s.thr[c];
         r.big[c] = s.big[c];
     }
-    L.p.hist = hist;
-    L.p.xall = xall;
-    L.p.solve = solve ? 1 : 0;
+    L.p.solve = 1;
     L.p.norm_inf = norm_inf;
-    if (!solve) {
-        if (!res_launch(h, L)) return false;
-        launch_res_finish(h.nrhs, h.plan.colfmt == COL_LOCAL16, h.plan.res_max_runs, h.stream, L.p,
-                          static_cast<double*>(x0_out), static_cast<ResSeen*>(h.d.res_seen.p));
-        h.res_numbers.passed(kend);
-        h.res_open = L.p.kbase;
-        ++h.res_loops;
-        res_time(h);
-        h.last_grid = L.grid;
-        h.last_loop_sweeps = kend;
-        return true;
-    }
     if (!res_launch(h, L)) return false;
-    if (x0_out) launch_res_settle(fp32, h.stream, xout, x0_out, (int64_t)h.a.n * h.nrhs, r.ctl, L.p.kbase);
+    if (x0_out)
+        launch_res_settle(fp32, h.stream, xout, x0_out, (int64_t)h.a.n * h.nrhs, r.ctl, L.p.kbase, more);
     ResCtl host;
     if (!res_wait(h, L, host)) return false;
     h.last_grid = L.grid;
-    h.last_loop_sweeps = kend;
     for (int c = 0; c < 4; ++c) {
         out.stop_k[c] = (int32_t)(host.stop[c] - L.p.kbase);
         out.nrm[c] = host.nrm[c];
@@ -242,6 +284,48 @@ bool run_resident(Handle& h, const SysDev& s, bool fp32, bool solve, int32_t ken
     out.done_k = 0;
     out.status = host.status;
     out.last_k = host.last_k;
+    return true;
+}
+
+bool run_resident_solve(Handle& h, const SysDev& s, bool fp32, int32_t maxit, int norm_inf, const void* x0, void* x0_out,
+                        void* xa, void* xb, SysState& out)
+{
+    // Each launch goes on from where the one before ran out of sweeps and
+    // tests that iterate again, with the same result; a column that has
+    // stopped stops at once.
+    const int32_t launches = std::max(res_launches(maxit), 1);
+    const bool direct = launches == 1 && x0 != x0_out;
+    SysDev t = s;
+    const void* from = x0;
+    void* to = direct ? x0_out : xa;
+    int32_t done = 0;
+    uint32_t stopped = 0;
+    double ms = 0.0;
+    for (int32_t q = 0; q < launches; ++q) {
+        const int32_t k1 = (int32_t)((int64_t)maxit * (q + 1) / launches);
+        const bool more = q + 1 < launches;
+        SysState st;
+        if (!res_solve(h, t, fp32, k1 - done, norm_inf, from, to, direct ? nullptr : x0_out, more, st)) return false;
+        ms += h.last_loop_ms;
+        out.done_k = 0;
+        out.status = st.status;
+        out.last_k = done + st.last_k;
+        const bool goes_on = more && st.status == JAC_NOT_CONVERGED;
+        for (int c = 0; c < 4; ++c) {
+            if ((stopped >> c) & 1u) continue;
+            out.stop_k[c] = done + st.stop_k[c];
+            out.nrm[c] = st.nrm[c];
+            if (c < h.nrhs && goes_on && st.nrm[c] <= s.thr[c]) {
+                stopped |= 1u << c;
+                t.thr[c] = std::numeric_limits<double>::infinity();
+            }
+        }
+        if (!goes_on) break;
+        done = k1;
+        from = to;
+        to = to == xa ? xb : xa;
+    }
+    if (h.opt.timing) h.last_loop_ms = ms;
     return true;
 }
 

@@ -173,8 +173,9 @@ hipError_t launch_res(void* fn, int grid, size_t lds, int32_t ldx, hipStream_t s
 // sweeps again (loc: explicit LDS positions; runs: largest number of
 // footprint runs of a tile).
 void launch_res_finish(int nrhs, bool loc, int32_t runs, hipStream_t st, ResParams p, double* x0, ResSeen* seen);
-// After a solve: x0 = xout unless the launch gave up.
+// After a solve: x0 = xout unless the launch gave up or, with more sweeps to
+// follow in another launch, ran out of its own.
 void launch_res_settle(bool fp32, hipStream_t st, const void* xout, void* x0, int64_t m, const ResCtl* ctl,
-                       uint32_t kbase);
+                       uint32_t kbase, bool more);
 
 }  // namespace jac

@@ -1028,9 +1028,9 @@ __global__ void __launch_bounds__(kResBlock) k_res_finish(ResParams P, int32_t l
 
 template <typename U>
 __global__ void __launch_bounds__(256) k_res_settle(const U* __restrict__ from, U* __restrict__ to, int64_t m,
-                                                    const ResCtl* __restrict__ ctl, uint32_t kbase)
+                                                    const ResCtl* __restrict__ ctl, uint32_t kbase, bool more)
 {
-    if (ctl->abort == kbase) return;
+    if (ctl->abort == kbase || (more && ctl->status == JAC_NOT_CONVERGED)) return;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
         to[i] = from[i];
 }
@@ -1097,13 +1097,15 @@ void launch_res_finish(int nrhs, bool loc, int32_t runs, hipStream_t st, ResPara
 }
 
 void launch_res_settle(bool fp32, hipStream_t st, const void* xout, void* x0, int64_t m, const ResCtl* ctl,
-                       uint32_t kbase)
+                       uint32_t kbase, bool more)
 {
     const int g = (int)std::min<int64_t>(std::max<int64_t>((m + 255) / 256, 1), 2048);
     if (fp32)
-        k_res_settle<<<g, 256, 0, st>>>(static_cast<const uint32_t*>(xout), static_cast<uint32_t*>(x0), m, ctl, kbase);
+        k_res_settle<<<g, 256, 0, st>>>(static_cast<const uint32_t*>(xout), static_cast<uint32_t*>(x0), m, ctl, kbase,
+                                            more);
     else
-        k_res_settle<<<g, 256, 0, st>>>(static_cast<const uint64_t*>(xout), static_cast<uint64_t*>(x0), m, ctl, kbase);
+        k_res_settle<<<g, 256, 0, st>>>(static_cast<const uint64_t*>(xout), static_cast<uint64_t*>(x0), m, ctl, kbase,
+                                            more);
     JAC_HIP(hipGetLastError());
 }
 

@@ -401,3 +401,44 @@ def test_fixed_sweeps_of_launches_that_give_up_are_done_again_on_the_device(name
         assert np.array_equal(u, v, equal_nan=True), (name, k)
     for h in hs:
         b.jac_destroy(h)
+
+
+def test_loops_longer_than_one_launch():
+    # a resident launch holds at most 65536 sweeps: longer loops go on in the
+    # next one, from the same iterate, with the stopped columns left alone
+    need_gpu()
+    b = B()
+    n = 200
+    A = sp.diags([2.0 * np.ones(n), -np.ones(n - 1), -np.ones(n - 1)], [0, 1, -1]).tocsr()
+    A.sort_indices()
+    rng = np.random.default_rng(2)
+    rhs = np.stack([np.sin(np.pi * np.arange(1, n + 1) / (n + 1)),            # some 150000 sweeps
+                    np.sin(70 * np.pi * np.arange(1, n + 1) / (n + 1))])      # some 30
+    s = W.CSRSystem(A.indptr.astype(np.int32), A.indices.astype(np.int32), A.data, rhs)
+    s1 = W.CSRSystem(s.row_ptr, s.col_idx, s.vals, rng.uniform(-1, 1, (1, n)))
+    hs = [make(s, 1, 1, opts={b.JAC_OPT_GRID: g}) for g in (1, 0)]
+    h1 = [make(s1, 1, 1, opts={b.JAC_OPT_GRID: g}) for g in (1, 0)]
+    out = []
+    for h, g in zip(hs, h1):
+        res = [sweep(h, 70000, 2), get_x(h, n, 2)]
+        for tol, maxit in ((1e-8, 1000000), (1e-8, 140000), (1e-2, 66000), (1e-8, 65536), (1e-8, 65537)):
+            b.jac_set_x(h, None)
+            st, sw, rr = b.jac_solve(h, tol, maxit)
+            res += [np.array(st), sw, rr, get_x(h, n, 2)]
+        assert res[2] == b.JAC_OK and 131072 < res[3][0] < 200000 and res[3][1] < 100 and res[6] == b.JAC_NOT_CONVERGED
+        b.jac_set_option(g, b.JAC_OPT_INNER_TOL, 1)
+        b.jac_set_option(g, b.JAC_OPT_INNER_MAX, 80000)
+        st, sw, rr = b.jac_solve(g, 1e-3, 200000, b.JAC_NORM_L2_REL, b.JAC_FP32_REFINE)
+        assert int(sw[0]) >= 80000
+        res += [np.array(st), sw, rr, get_x(g, n)]
+        gb = torch.empty(n, dtype=torch.float64, device="cuda")
+        gv = torch.empty(s1.nnz, dtype=torch.float64, device="cuda")
+        b.jac_adjoint(g, 70000, 5000, torch.from_numpy(rhs[1]).cuda(), gb, gv)
+        res += [gb.cpu().numpy(), gv.cpu().numpy(), get_x(g, n)]
+        out.append(res)
+    # 2 launches of sweeps; 3, 3, 1 or 2, 1 and 2 of solves at least; the same of the refinement and the forward
+    assert b.jac_get_info(hs[1])["resident_loops"] >= 11 and b.jac_get_info(h1[1])["resident_loops"] >= 4
+    for k, (u, v) in enumerate(zip(*out)):
+        assert np.array_equal(u, v), k
+    for h in hs + h1:
+        b.jac_destroy(h)
