@@ -30,7 +30,8 @@
  *   - Synchronous semantics: every component of x_{k+1} is computed from x_k
  *     (two buffers, never in place).
  *   - One handle must not be used by two threads at once.  The library has
- *     no other mutable global state except the autotuner's cache (guarded).
+ *     no other mutable global state except the autotuner's cache and a note
+ *     per device of the handle whose resident loop is on it (both guarded).
  */
 #ifndef LIBJACOBI_H
 #define LIBJACOBI_H
@@ -89,7 +90,10 @@ typedef enum {
                                 device at once, the tile, block and grid
                                 options leave it open and a call has eight
                                 sweeps or more: every sweep in one resident
-                                launch; else one launch per sweep.  Iterates, norms and stop
+                                launch, beside those of other streams where the
+                                device holds both and after them else; one
+                                launch per sweep otherwise, also while another
+                                stream holds its resident launch back.  Iterates, norms and stop
                                 sweeps are the same bits.  1 = persistent
                                 cooperative loop with a grid barrier per sweep     */
     JAC_OPT_WG_PER_CU = 5,   /* persistent loop: workgroups per CU, default 2 (0 =

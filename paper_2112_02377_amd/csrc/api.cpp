@@ -68,6 +68,7 @@ void Handle::require_plan() const
 
 Handle::~Handle()
 {
+    res_leave();
     for (auto& e : ev)
         if (e) (void)hipEventDestroy(e);
     if (pev) (void)hipEventDestroy(pev);

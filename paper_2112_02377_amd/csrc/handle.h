@@ -91,6 +91,7 @@ struct Handle {
     bool planned = false;
     ResNumbers res_numbers;        // of the resident launches
     ResRetry res_retry;            // after one that gave up
+    bool res_ordinary = false;     // cooperative launches were refused
     int32_t res_loops = 0;         // resident launches not known to have given up
     uint32_t res_gave_up = 0;      // of the launches not waited for, those known to have given up
     uint32_t res_open = 0;         // kbase of the last such launch, until it is known to have run
@@ -139,6 +140,7 @@ struct Handle {
     void require_plan() const;
     int lds_fp_bytes(bool fp32) const;
     int lds_tab() const;
+    void res_leave();              // gives the device's place for resident launches back
     void res_poll();               // takes note of resident launches that ended since the last call
 };
 

@@ -1,7 +1,10 @@
 // Host side of the resident loop: which loops take it, its buffers, launch
 // and result.
 #include <algorithm>
+#include <chrono>
 #include <limits>
+#include <mutex>
+#include <thread>
 
 #include "handle.h"
 #include "launch.h"
@@ -11,7 +14,7 @@ namespace jac {
 
 namespace {
 
-// A loop this short costs less as per-sweep launches: a cooperative launch
+// A loop this short costs less as per-sweep launches: a resident launch
 // takes about 20 us from queue to queue, a per-sweep launch of a small
 // system 5.4 us against 1.5-2.5 us for a resident sweep.
 constexpr int32_t kResMinSweeps = 8;
@@ -45,6 +48,82 @@ size_t res_lds(const Plan& pl, int32_t ldx, int nrhs, size_t elem, int width, bo
     return std::max({x + b, (size_t)pl.res_max_runs * 8, decider});
 }
 
+// Resident launches on a device that may not have ended, one entry per stream
+// (a stream runs one at a time).  Workgroups of a launch wait for each other,
+// so two launches may be on the device together only if both fit whole: a
+// launch joins others if their shares of the device and the largest workgroup's
+// share of a compute unit make no more than 1 -- then some compute unit always
+// has room for the next workgroup, whatever the order.
+struct Loop {
+    const Handle* holder;
+    hipStream_t stream;
+    const ResSeen* seen;            // of the holder
+    uint32_t kbase;                 // its last launch
+    double share, wg;
+};
+constexpr int kMaxDevices = 64;
+std::mutex g_loops_mutex;
+std::vector<Loop> g_loops[kMaxDevices];
+
+// Whether a launch of that share may go on the handle's stream.  Waits for
+// room, but only behind launches that are running: one behind other work on
+// its stream may take any time.  (Per-sweep launches beside a resident loop
+// that fills the device slow both: eight streams' sweeps at 64^3 take 745 us
+// a hundred so, 370 one loop after the other.)
+enum class Entry { no, beside, alone };
+Entry loops_enter(const Handle& h, double share, double wg)
+{
+    if (h.device < 0 || h.device >= kMaxDevices) return Entry::no;
+    int held = 0;
+    for (int tries = 0; tries < 20000; ++tries) {
+        {
+            std::lock_guard<std::mutex> lock(g_loops_mutex);
+            std::vector<Loop>& v = g_loops[h.device];
+            Loop me{&h, h.stream, static_cast<const ResSeen*>(h.d.res_seen.p), h.res_numbers.next, share, wg};
+            double total = 0.0, most = wg;
+            bool running = true;
+            for (auto q = v.begin(); q != v.end();) {
+                if (__atomic_load_n(&q->seen->ended, __ATOMIC_ACQUIRE) == q->kbase) {
+                    q = v.erase(q);
+                } else if (q->holder == &h || (q->stream == h.stream && h.stream != hipStreamPerThread)) {
+                    me.share = std::max(me.share, q->share);
+                    me.wg = std::max(me.wg, q->wg);
+                    ++q;
+                } else {
+                    total += q->share;
+                    most = std::max(most, q->wg);
+                    running = running && __atomic_load_n(&q->seen->started, __ATOMIC_RELAXED) == q->kbase;
+                    ++q;
+                }
+            }
+            if (total == 0.0 || total + me.share + std::max(most, me.wg) <= 1.0) {
+                v.erase(std::remove_if(v.begin(), v.end(),
+                                       [&](const Loop& q) {
+                                           return q.holder == &h ||
+                                                  (q.stream == h.stream && h.stream != hipStreamPerThread);
+                                       }),
+                        v.end());
+                v.push_back(me);
+                return total == 0.0 ? Entry::alone : Entry::beside;
+            }
+            held = running ? 0 : held + 1;       // a launch takes some time to start, too
+            if (held > 10) return Entry::no;
+        }
+        std::this_thread::sleep_for(std::chrono::microseconds(20));
+    }
+    return Entry::no;
+}
+
+// Ordinary launches, since cooperative ones run one after another, behind any
+// that its stream holds back, and one process at a time: four threads with
+// solves at 20^3 take 0.50 ms a solve, 1.8 as cooperative launches (1.27 per
+// sweep); 33^3 1.4, 4.1 and 3.0; 64^3, of which two do not fit, 20.7, 22.9
+// and 32.  A call of ten sweeps at 16^3 takes 81 us, 101 cooperative.  But
+// sweeps are about 1% slower (2216 at 65^3: 12.25 and 12.12 ms, 1160 at 20^3:
+// 2.84 and 2.81; cause not found), so a launch that may be long is
+// cooperative where no other stream's is on the device.
+constexpr int32_t kResLong = 1024;
+
 // What a launch needs besides its system; ok: the plan fits the chip and the
 // handle's options leave the choice open.
 struct ResLaunch {
@@ -53,6 +132,7 @@ struct ResLaunch {
     int grid = 0;
     size_t lds = 0;
     int32_t ldx = 0;
+    double share = 0.0, wg = 0.0;   // of the device, and a workgroup's of a compute unit
     ResParams p{};
 };
 
@@ -90,6 +170,10 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     }
     L.grid = pl.ntiles + kResDeciders;
     if (L.grid > (int64_t)nb * num_cus()) return L;
+    // the dispatcher deals workgroups to groups of eight compute units in turn
+    const int groups = std::max(num_cus() / 8, 1);
+    L.share = (double)((L.grid + groups - 1) / groups) / (8.0 * nb);
+    L.wg = 1.0 / nb;
     if (!h.res_retry.now()) return L;
 
     DeviceArrays& d = h.d;
@@ -145,9 +229,13 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     return L;
 }
 
-// Puts it on the stream; false (and not tried again for a while) if it was refused.
+// Puts it on the stream; false if other streams' loops leave it no room, or
+// (and not tried again for a while) if it was refused.
 bool res_launch(Handle& h, ResLaunch& L)
 {
+    const Entry entry = loops_enter(h, L.share, L.wg);
+    if (entry == Entry::no) return false;
+    L.p.seen = static_cast<ResSeen*>(h.d.res_seen.p);
     L.p.kbase = h.res_numbers.next;
     L.p.arrive = h.res_numbers.arrived + (uint32_t)L.grid;
     if (h.opt.timing) {
@@ -155,8 +243,17 @@ bool res_launch(Handle& h, ResLaunch& L)
             if (!e) JAC_HIP(hipEventCreate(&e));
         JAC_HIP(hipEventRecord(h.ev[0], h.stream));
     }
-    if (launch_res(L.fn, L.grid, L.lds, L.ldx, h.stream, L.p) != hipSuccess) {
+    bool launched = false;
+    if (entry == Entry::alone && L.p.solve && L.p.kend > kResLong && !h.res_ordinary) {
+        launched = launch_res(L.fn, L.grid, L.lds, L.ldx, h.stream, L.p, true) == hipSuccess;
+        if (!launched) {
+            (void)hipGetLastError();
+            h.res_ordinary = true;          // refused while another process has cooperative launches
+        }
+    }
+    if (!launched && launch_res(L.fn, L.grid, L.lds, L.ldx, h.stream, L.p, false) != hipSuccess) {
         (void)hipGetLastError();
+        h.res_leave();
         h.res_retry.failed();
         return false;
     }
@@ -179,6 +276,7 @@ bool res_wait(Handle& h, const ResLaunch& L, ResCtl& host)
 {
     JAC_HIP(hipMemcpyAsync(&host, L.p.sys.ctl, sizeof(ResCtl), hipMemcpyDeviceToHost, h.stream));
     h.sync();
+    h.res_leave();
     if (host.abort == L.p.kbase) {
         h.res_numbers.passed(L.p.kend);
         h.res_retry.failed();               // do not wait that long again soon
@@ -192,6 +290,14 @@ bool res_wait(Handle& h, const ResLaunch& L, ResCtl& host)
 }
 
 }  // namespace
+
+void Handle::res_leave()
+{
+    if (device < 0 || device >= kMaxDevices) return;
+    std::lock_guard<std::mutex> lock(g_loops_mutex);
+    std::vector<Loop>& v = g_loops[device];
+    v.erase(std::remove_if(v.begin(), v.end(), [&](const Loop& q) { return q.holder == this; }), v.end());
+}
 
 void Handle::res_poll()
 {
@@ -223,7 +329,7 @@ static bool res_sweeps(Handle& h, const SysDev& s, int32_t kend, double* hist, c
     L.p.xall = xall;
     if (!res_launch(h, L)) return false;
     launch_res_finish(h.nrhs, h.plan.colfmt == COL_LOCAL16, h.plan.res_max_runs, h.stream, L.p,
-                      static_cast<double*>(x0_out), static_cast<ResSeen*>(h.d.res_seen.p));
+                      static_cast<double*>(x0_out));
     h.res_numbers.passed(kend);
     h.res_open = L.p.kbase;
     ++h.res_loops;

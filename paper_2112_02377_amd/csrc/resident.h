@@ -80,8 +80,9 @@ struct ResCtl {
     uint64_t redo_done;
 };
 
-// What the host learns of launches it does not wait for (pinned memory).
+// What the host learns of launches without waiting for them (pinned memory).
 struct ResSeen {
+    uint32_t started;               // kbase of the last launch that started
     uint32_t ended;                 // kbase of the last launch that ended
     uint32_t gave_up;               // launches that gave up
 };
@@ -156,6 +157,7 @@ struct ResParams {
     // nullable: every iterate, x_k at k * n (fixed sweeps of one FP64 column);
     // adjoint: mu of the kend + 1 steps, the first (mu_K) last
     void* xall;
+    ResSeen* seen;
     uint32_t kbase;                 // see ResCtl
     uint32_t arrive;                // ctl->arrived once every workgroup of this launch has arrived
     uint32_t wait;                  // longest wait for another workgroup, in ticks of the 100 MHz clock
@@ -168,11 +170,11 @@ void* res_kernel(bool fp32, int nrhs, int width, int slices, bool explicit_cols)
 // Reverse sweeps of the adjoint (FP64, one column, shift table).
 void* res_adjoint_kernel(int width, int slices);
 // ldx: x entries in LDS per right-hand side; lds: see res_lds in resident.cpp
-hipError_t launch_res(void* fn, int grid, size_t lds, int32_t ldx, hipStream_t st, ResParams p);
+hipError_t launch_res(void* fn, int grid, size_t lds, int32_t ldx, hipStream_t st, ResParams p, bool cooperative);
 // After a launch of fixed FP64 sweeps: x0 = xout, or, if it gave up, its
 // sweeps again (loc: explicit LDS positions; runs: largest number of
 // footprint runs of a tile).
-void launch_res_finish(int nrhs, bool loc, int32_t runs, hipStream_t st, ResParams p, double* x0, ResSeen* seen);
+void launch_res_finish(int nrhs, bool loc, int32_t runs, hipStream_t st, ResParams p, double* x0);
 // After a solve: x0 = xout unless the launch gave up or, with more sweeps to
 // follow in another launch, ran out of its own.
 void launch_res_settle(bool fp32, hipStream_t st, const void* xout, void* x0, int64_t m, const ResCtl* ctl,

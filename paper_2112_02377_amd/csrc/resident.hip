@@ -1,5 +1,5 @@
 // Resident sweep loop of libjacobi for gfx950: every sweep of a system in one
-// cooperative launch, with the matrix held in registers.
+// launch, with the matrix held in registers.
 //
 // A system whose tiles all fit the chip at once (the 128 MB of vector
 // registers hold the slot values) is swept without a launch per sweep and
@@ -55,6 +55,10 @@ namespace jac {
 namespace {
 
 constexpr int32_t kNever = kRunning;
+// Longest wait for all workgroups of a launch to be there, 0.2 s: they are as
+// soon as other kernels on the device leave room, unless another process's
+// resident launch and this one each keep what the other needs.
+constexpr uint32_t kArriveTicks = 20000000;
 
 template <typename T> struct Bits;
 template <> struct Bits<double> {
@@ -109,7 +113,7 @@ __device__ __forceinline__ void lds_barrier()
 struct Patience {
     uint64_t t0 = 0;
     uint32_t n = 0;
-    __device__ __forceinline__ bool out(const ResParams& P)
+    __device__ __forceinline__ bool out(const ResParams& P, uint32_t most = ~0u)
     {
         ResCtl* ctl = P.sys.ctl;
         const uint32_t kbase = P.kbase;
@@ -117,7 +121,7 @@ struct Patience {
         const uint64_t t = wall_clock64();
         if (t0 == 0) t0 = t;
         if (ldc(&ctl->abort) == kbase) return true;
-        if (P.wait == 0 || t - t0 > P.wait) {
+        if (P.wait == 0 || t - t0 > min(P.wait, most)) {
             stc(&ctl->abort, kbase);
             return true;
         }
@@ -137,7 +141,7 @@ __device__ __forceinline__ bool res_arrive(const ResParams& P, int32_t* ok)
         Patience wait;
         bool in = true;
         while ((int32_t)(ldc(&ctl->arrived) - P.arrive) < 0)
-            if (wait.out(P)) {
+            if (wait.out(P, kArriveTicks)) {
                 in = false;
                 break;
             }
@@ -873,6 +877,7 @@ k_resident(ResParams P, int32_t ldx)
         if (wg == ntiles && threadIdx.x == 0) {
             stc(&P.sys.ctl->status, (int32_t)JAC_OK);
             stc(&P.sys.ctl->last_k, -1);
+            __hip_atomic_store(&P.seen->started, P.kbase, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             stc(&P.sys.ctl->redo_sweeps, 0u);
             stc(&P.sys.ctl->redo_next, (uint64_t)0);
             stc(&P.sys.ctl->redo_done, (uint64_t)0);
@@ -898,8 +903,7 @@ k_resident(ResParams P, int32_t ldx)
 // columns searched through the footprint's runs: some 60 us a sweep at 65^3
 // would do, and this one never has to be fast.)
 template <int NRHS>
-__global__ void __launch_bounds__(kResBlock) k_res_finish(ResParams P, int32_t loc, int32_t max_runs, double* x0_out,
-                                                          ResSeen* seen)
+__global__ void __launch_bounds__(kResBlock) k_res_finish(ResParams P, int32_t loc, int32_t max_runs, double* x0_out)
 {
     extern __shared__ __align__(16) char smem[];
     __shared__ double red[kResRed];
@@ -909,7 +913,8 @@ __global__ void __launch_bounds__(kResBlock) k_res_finish(ResParams P, int32_t l
     ResCtl* ctl = S.ctl;
     const int32_t n = S.n;
     const bool gave_up = ldc(&ctl->abort) == P.kbase;
-    if (seen && blockIdx.x == 0 && threadIdx.x == 0) {
+    ResSeen* seen = P.seen;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         // host memory: plain loads and stores; launches of one stream, so one writer at a time
         if (gave_up)
             __hip_atomic_store(&seen->gave_up, __hip_atomic_load(&seen->gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1,
@@ -1079,20 +1084,21 @@ void* res_kernel(bool fp32, int nrhs, int width, int slices, bool explicit_cols)
                 : pick_rhs<double>(nrhs, width, slices, explicit_cols);
 }
 
-hipError_t launch_res(void* fn, int grid, size_t lds, int32_t ldx, hipStream_t st, ResParams p)
+hipError_t launch_res(void* fn, int grid, size_t lds, int32_t ldx, hipStream_t st, ResParams p, bool cooperative)
 {
     void* args[] = {&p, &ldx};
-    return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(kResBlock), args, (unsigned)lds, st);
+    if (cooperative) return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(kResBlock), args, (unsigned)lds, st);
+    return hipLaunchKernel(fn, dim3(grid), dim3(kResBlock), args, lds, st);
 }
 
-void launch_res_finish(int nrhs, bool loc, int32_t runs, hipStream_t st, ResParams p, double* x0, ResSeen* seen)
+void launch_res_finish(int nrhs, bool loc, int32_t runs, hipStream_t st, ResParams p, double* x0)
 {
     const int64_t m = (int64_t)p.sys.n * nrhs;
     const int g = (int)std::min<int64_t>((m + kResBlock - 1) / kResBlock, 2048);
     const size_t lds = (size_t)runs * 8;
-    if (nrhs == 1) k_res_finish<1><<<g, kResBlock, lds, st>>>(p, loc, runs, x0, seen);
-    else if (nrhs == 2) k_res_finish<2><<<g, kResBlock, lds, st>>>(p, loc, runs, x0, seen);
-    else k_res_finish<4><<<g, kResBlock, lds, st>>>(p, loc, runs, x0, seen);
+    if (nrhs == 1) k_res_finish<1><<<g, kResBlock, lds, st>>>(p, loc, runs, x0);
+    else if (nrhs == 2) k_res_finish<2><<<g, kResBlock, lds, st>>>(p, loc, runs, x0);
+    else k_res_finish<4><<<g, kResBlock, lds, st>>>(p, loc, runs, x0);
     JAC_HIP(hipGetLastError());
 }
 

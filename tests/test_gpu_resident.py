@@ -442,3 +442,49 @@ def test_loops_longer_than_one_launch():
         assert np.array_equal(u, v), k
     for h in hs + h1:
         b.jac_destroy(h)
+
+
+@pytest.mark.parametrize("edge,joins", [(16, True), (64, False)])
+def test_a_loop_does_not_wait_for_other_streams(edge, joins):
+    # a resident launch that its stream holds back must not hold back the
+    # loops of other streams: they are on the device beside it where both fit
+    # whole, else launched per sweep until it has ended
+    need_gpu()
+    b = B()
+    s = W.laplace7(edge, workload=1)
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    hs = []
+    for st in (one, two):
+        with torch.cuda.stream(st):
+            hs.append(make(s, 1, 2))
+            b.jac_sweep(hs[-1], 50, None)
+        torch.cuda.synchronize()
+    with torch.cuda.stream(two):
+        b.jac_set_x(hs[1], None)
+        st, sw, rr = b.jac_solve(hs[1], 1e-3, 5000)
+        want = get_x(hs[1], s.n)
+    torch.cuda.synchronize()
+
+    def ran():
+        return [b.jac_get_info(h)["resident_loops"] for h in hs]
+
+    assert ran() == [1, 2]
+    with torch.cuda.stream(one):
+        before = busy_stream(500)
+        b.jac_sweep(hs[0], 50, None)
+        b.jac_sweep(hs[0], 50, None)
+    with torch.cuda.stream(two):
+        b.jac_set_x(hs[1], None)
+        got = b.jac_solve(hs[1], 1e-3, 5000)
+    assert not before.query()
+    assert got == (st, sw, rr) and np.array_equal(get_x(hs[1], s.n), want)
+    torch.cuda.synchronize()
+    assert ran() == [3, 3 if joins else 2]
+    with torch.cuda.stream(two):
+        b.jac_solve(hs[1], 1e-4, 5000)
+        assert ran() == [3, 4 if joins else 3]
+        b.jac_destroy(hs.pop(0))
+        b.jac_sweep(hs[0], 50, None)
+    torch.cuda.synchronize()
+    assert ran() == [5 if joins else 4]
+    b.jac_destroy(hs[0])
