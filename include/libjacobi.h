@@ -129,7 +129,9 @@ typedef enum {
                                 column per slot, if that streams fewer bytes
                                 over the whole split; 0: never.  Results are
                                 bit-identical either way                       */
-    JAC_OPT_GRID = 13,        /* 1 and 2 keep one launch per sweep.  Workgroups of
+    JAC_OPT_GRID = 13,        /* 1 and 2 keep one launch per sweep (unless
+                                jac_autotune set them, having found the
+                                resident loop faster).  Workgroups of
                                 the one-launch-per-sweep loop of a
                                 single system (each of the eight XCDs sweeps a
                                 contiguous share of the tiles of about equal
@@ -360,8 +362,8 @@ jac_status jac_adjoint(jac_handle h, int32_t K, int32_t ckpt_every, const double
 
 /* Time candidate tile shapes (rows per tile, threads per workgroup) on this
  * handle and keep the fastest, with the launch grid of per-sweep launches
- * (a workgroup per tile or one resident round) when JAC_OPT_GRID is left
- * automatic; then time FP32 refinements from x = 0 to relative 1e-10 for
+ * (a workgroup per tile or one resident round) and the choice between those
+ * and the resident loop when JAC_OPT_GRID is left automatic; then time FP32 refinements from x = 0 to relative 1e-10 for
  * candidate inner stop parameters (JAC_OPT_INNER_TOL in {1e-3, 1e-4, 1e-5,
  * 1e-6}, JAC_OPT_INNER_MAX in {64, 256, 1024, 4096}) and keep the quickest.
  * x is restored afterwards.  The choices are cached on disk under

@@ -925,7 +925,8 @@ jac_status jac_set_option(jac_handle h, jac_option opt, int64_t v)
             o.tables = (int32_t)v; break;
         case JAC_OPT_GRID:
             if (v < 0 || v > 2) fail(JAC_E_INVALID, "grid: 0, 1 or 2");
-            o.grid = (int32_t)v; break;
+            o.grid = (int32_t)v;
+            h->res_tuned = false; break;
         default: fail(JAC_E_INVALID, "unknown option");
         }
         return JAC_OK;

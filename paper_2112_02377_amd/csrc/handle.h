@@ -91,6 +91,7 @@ struct Handle {
     bool planned = false;
     ResNumbers res_numbers;        // of the resident launches
     ResRetry res_retry;            // after one that gave up
+    bool res_tuned = false;        // opt.grid is the autotuner's, which found the resident loop faster
     bool res_ordinary = false;     // cooperative launches were refused
     int32_t res_loops = 0;         // resident launches not known to have given up
     uint32_t res_gave_up = 0;      // of the launches not waited for, those known to have given up

@@ -142,7 +142,7 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     h.res_poll();
     // Options that name a launch shape keep per-sweep launches (or the
     // persistent loop); the norm is summed in the order of 256 threads.
-    if (h.opt.loop != 0 || h.opt.grid != 0 || h.opt.block != kResBlock || kend < kResMinSweeps || kend > kResMaxSweeps) return L;
+    if (h.opt.loop != 0 || (h.opt.grid != 0 && !h.res_tuned) || h.opt.block != kResBlock || kend < kResMinSweeps || kend > kResMaxSweeps) return L;
     const bool loc = pl.colfmt == COL_LOCAL16;
     const bool tabg = pl.colfmt == COL_TABG && !pl.res_run0.empty();
     if (!tabg && (adjoint || (!loc && pl.colfmt != COL_TABL))) return L;

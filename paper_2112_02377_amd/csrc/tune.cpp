@@ -1,12 +1,15 @@
 // Autotuner: times candidate tile shapes (rows per tile) and workgroup sizes
-// (and, when left automatic, the launch grid of per-sweep launches) for the
-// fused sweep on the handle's own matrix and split, keeps the fastest,
+// (and, when left automatic, the launch grid of per-sweep launches and the
+// resident loop) for the fused sweep on the handle's own matrix and split,
+// keeps the fastest,
 // then times candidate inner stop parameters of the FP32 refinement (inner
 // relative tolerance tau and sweep cap m_max) on the tuned shape and keeps
 // the pair that reduces the FP64 residual fastest.  The choices are cached in
 // a text file named by $JAC_TUNE_CACHE, one line per key
 // "n nnz nrhs mode nparts sx sy sz fp32" -> "tile_rows block us_per_sweep",
-// "grid <key>" -> "grid 0 us_per_sweep" and "refine <key>" -> "tau_x1e9 m_max
+// "grid <key>" -> "grid loop us_per_sweep" (loop: 1 the resident loop was
+// fastest, at this shape, 2 per-sweep launches were, 0 it was not timed, as in
+// lines of earlier versions) and "refine <key>" -> "tau_x1e9 m_max
 // decades_per_ms".
 #include <cstdio>
 #include <cstdlib>
@@ -93,6 +96,29 @@ double time_sweeps(Handle& h, int32_t sweeps)
     return h.last_loop_ms;
 }
 
+// Average duration of a fixed sweep in the resident loop, ms (the best of two
+// runs after an unrecorded one), or a negative number where it does not take
+// the handle.  A short loop would count the launch, about 10 us, too often.
+double time_resident(Handle& h, int32_t sweeps)
+{
+    const int32_t K = std::max(sweeps, 64);
+    const int32_t timing = h.opt.timing, grid = h.opt.grid;
+    h.opt.grid = 0;
+    double best = -1.0;
+    for (int run = 0; run < 3; ++run) {
+        h.opt.timing = 1;
+        const bool ran = run_resident_sweeps(h, h.sysdev(false), K, nullptr, h.d.x0.p, h.d.x1.p, h.d.x0.p) == K;
+        h.opt.timing = timing;
+        if (!ran) {
+            best = -1.0;
+            break;
+        }
+        if (run > 0 && (best < 0.0 || h.last_loop_ms / K < best)) best = h.last_loop_ms / K;
+    }
+    h.opt.grid = grid;
+    return best;
+}
+
 // Inner stop parameters of the FP32 refinement: relative tolerance (x1e-9)
 // and sweep cap.  Every pair runs two trials, refinements from x = 0 to the
 // relative 2-norm kTuneTol within a sweep budget, and scores the faster by
@@ -106,10 +132,11 @@ const int64_t kTauE9[] = {1000000, 100000, 10000, 1000};
 const int32_t kInnerMax[] = {64, 256, 1024, 4096};
 constexpr double kTuneTol = 1e-10;   // the accuracy FP64 refinement is there for
 
-void tune_refine(Handle& h, int32_t sweeps_per_trial, const std::string& key)
+// fresh: the shape was timed anew, and what is stored belongs to another.
+void tune_refine(Handle& h, int32_t sweeps_per_trial, const std::string& key, bool fresh, bool store)
 {
     int64_t tau = 0, mmax = 0;
-    if (cache_lookup("refine " + key, tau, mmax)) {
+    if (!fresh && cache_lookup("refine " + key, tau, mmax)) {
         h.opt.inner_tol = (double)tau * 1e-9;
         h.opt.inner_max = (int32_t)mmax;
         return;
@@ -161,7 +188,7 @@ void tune_refine(Handle& h, int32_t sweeps_per_trial, const std::string& key)
     h.opt.timing = timing;
     h.opt.inner_tol = (double)pick_tau * 1e-9;
     h.opt.inner_max = pick_max;
-    cache_store("refine " + key, pick_tau, pick_max, best);
+    if (store) cache_store("refine " + key, pick_tau, pick_max, best);
 }
 
 }  // namespace
@@ -185,12 +212,19 @@ extern "C" jac_status jac_autotune(jac_handle hp, int32_t sweeps_per_trial)
         h.get_x_dev(static_cast<double*>(xs.p));
         // the launch grid of per-sweep launches is tuned with the shape when
         // the caller left it automatic (JAC_OPT_GRID = 0): a workgroup per
-        // tile or one resident round
-        const bool tune_grid = h.opt.grid == 0;
-        int64_t rows = 0, block = 0, grid = 0, unused = 0;
-        if (cache_lookup(key, rows, block) && (!tune_grid || cache_lookup("grid " + key, grid, unused))) {
+        // tile or one resident round; and so is the resident loop, which a
+        // grid of the caller's own excludes
+        const bool tune_grid = h.opt.grid == 0 || h.res_tuned;
+        const bool tune_loop = tune_grid && h.opt.loop == 0;
+        int64_t rows = 0, block = 0, grid = 0, loop = 0;
+        const bool stored = cache_lookup(key, rows, block), grid_stored = cache_lookup("grid " + key, grid, loop);
+        // a shape stored for the resident loop is not one for per-sweep launches
+        const bool other = stored && grid_stored && loop == 1 && !tune_loop;
+        const bool fresh = !stored || other || (tune_grid && !grid_stored) || (tune_loop && loop == 0);
+        if (!fresh) {
             h.opt.block = (int32_t)block;
             if (tune_grid) h.opt.grid = (int32_t)grid;
+            h.res_tuned = tune_loop && loop == 1;
             if (rows != h.opt.tile_rows) {
                 h.opt.tile_rows = (int32_t)rows;
                 h.replan(h.part_mode, h.part_nparts, sub);
@@ -199,6 +233,7 @@ extern "C" jac_status jac_autotune(jac_handle hp, int32_t sweeps_per_trial)
             double best = 1e300;
             Cand pick = {h.opt.tile_rows, h.opt.block};
             int32_t pick_grid = h.opt.grid;
+            bool resident = false;
             const int32_t grids[2] = {1, 2};
             for (const Cand& c : kCands) {
                 if (c.tile_rows != h.opt.tile_rows) {
@@ -206,26 +241,40 @@ extern "C" jac_status jac_autotune(jac_handle hp, int32_t sweeps_per_trial)
                     h.replan(h.part_mode, h.part_nparts, sub);
                 }
                 h.opt.block = c.block;
+                // of this shape: its own best grid goes with the resident loop
+                double shape_best = 1e300;
+                int32_t shape_grid = h.opt.grid;
                 for (int g = 0; g < (tune_grid ? 2 : 1); ++g) {
                     if (tune_grid) h.opt.grid = grids[g];
-                    const double ms = time_sweeps(h, sweeps_per_trial);
-                    if (ms < best) {
-                        best = ms;
-                        pick = c;
-                        pick_grid = h.opt.grid;
+                    const double ms = time_sweeps(h, sweeps_per_trial) / sweeps_per_trial;
+                    if (ms < shape_best) {
+                        shape_best = ms;
+                        shape_grid = h.opt.grid;
                     }
+                }
+                const double res = tune_loop ? time_resident(h, sweeps_per_trial) : -1.0;
+                const bool faster = res >= 0.0 && res < shape_best;
+                if (faster) shape_best = res;
+                if (shape_best < best) {
+                    best = shape_best;
+                    pick = c;
+                    pick_grid = shape_grid;
+                    resident = faster;
                 }
             }
             h.opt.block = pick.block;
             h.opt.grid = pick_grid;
+            h.res_tuned = resident;
             if (pick.tile_rows != h.opt.tile_rows) {
                 h.opt.tile_rows = pick.tile_rows;
                 h.replan(h.part_mode, h.part_nparts, sub);
             }
-            cache_store(key, pick.tile_rows, pick.block, best * 1e3 / sweeps_per_trial);
-            if (tune_grid) cache_store("grid " + key, pick_grid, 0, best * 1e3 / sweeps_per_trial);
+            if (!other) {
+                cache_store(key, pick.tile_rows, pick.block, best * 1e3);
+                if (tune_grid) cache_store("grid " + key, pick_grid, tune_loop ? (resident ? 1 : 2) : 0, best * 1e3);
+            }
         }
-        tune_refine(h, sweeps_per_trial, key);
+        tune_refine(h, sweeps_per_trial, key, fresh, !other);
         // the refinement trials left their residual in the norm partials and
         // their iterates in x: restore the caller's x (the partials of the
         // next loop are rewritten before they are read)

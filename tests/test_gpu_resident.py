@@ -488,3 +488,44 @@ def test_a_loop_does_not_wait_for_other_streams(edge, joins):
     torch.cuda.synchronize()
     assert ran() == [5 if joins else 4]
     b.jac_destroy(hs[0])
+
+
+def test_autotune_keeps_the_resident_loop(tmp_path, monkeypatch):
+    # a tuned handle of a system that fits the device stays on the loop it
+    # runs by default, from the cache too, and with a cache of a time when
+    # the loop was not among the candidates; a grid of the caller's own keeps
+    # per-sweep launches
+    need_gpu()
+    b = B()
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("JAC_TUNE_CACHE", str(cache))
+    s = W.laplace7(24, workload=1)
+
+    def tuned(grid=0):
+        h = make(s, 2, 4, opts={b.JAC_OPT_GRID: grid})
+        b.jac_autotune(h, 20)
+        ran = b.jac_get_info(h)["resident_loops"]
+        b.jac_set_x(h, None)
+        st, sw, rr = b.jac_solve(h, 1e-8, 10000)
+        info = b.jac_get_info(h)
+        x = get_x(h, s.n)
+        return h, info["resident_loops"] - ran, int(sw[0]), x, len(cache.read_text().splitlines())
+
+    _, xr, kr, _ = ref.solve(s.row_ptr, s.col_idx, s.vals, s.b[0], 1e-8, 10000)
+    handles = []
+    for k, (grid, loops, lines) in enumerate(((0, 1, 3), (0, 1, 3), (1, 0, 3), (0, 1, 3), (0, 1, 6))):
+        if k == 4:
+            cache.write_text(cache.read_text().replace("|1 1 ", "|1 0 ").replace("|2 1 ", "|2 0 "))
+        h, ran, sweeps, x, stored = tuned(grid)
+        handles.append(h)
+        assert (ran, sweeps, stored) == (loops, kr, lines), k
+        assert rel_inf(x[0], xr) <= 1e-10
+        if grid == 0:
+            assert b.jac_get_option(h, b.JAC_OPT_BLOCK) == 256 and b.jac_get_option(h, b.JAC_OPT_GRID) in (1, 2)
+    b.jac_set_option(handles[0], b.JAC_OPT_GRID, 1)
+    ran = b.jac_get_info(handles[0])["resident_loops"]
+    b.jac_set_x(handles[0], None)
+    b.jac_solve(handles[0], 1e-8, 10000)
+    assert b.jac_get_info(handles[0])["resident_loops"] == ran
+    for h in handles:
+        b.jac_destroy(h)
