@@ -189,7 +189,7 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
             (void)hipGetLastError();
             return L;                       // per-sweep launches need none of it
         }
-        h.res_numbers = ResNumbers();
+        h.res_numbers.zeroed();
         clear = true;
     }
     if (clear) launch_zero_u32(static_cast<uint32_t*>(d.res_work.p), (int32_t)(sizeof(ResCtl) / 4), h.stream);

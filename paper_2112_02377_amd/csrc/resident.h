@@ -101,6 +101,9 @@ struct ResNumbers {
         *this = ResNumbers();
         return true;
     }
+    // The words were zeroed for another reason (a new buffer): numbers go on,
+    // so that a launch is never taken for an earlier one that had its number.
+    void zeroed() { arrived = 0; }
     // After a launch whose last sweep was number `last`: the tiles ran ahead
     // of it by less than kResPart sweeps.
     void passed(int32_t last) { next += (uint32_t)last + 2 * kResPart; }

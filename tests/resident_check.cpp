@@ -7,7 +7,9 @@
 //   split (mode 1 JB, 2 JBO, 3 JSS), lanes of absent rows and slices included
 //    or: resident_check numbers sweeps
 //   what a solve left in the control words reads as "not yet" to every later
-//   launch, over launches of that many fixed sweeps whose numbers pass 2^32
+//   launch, over launches of that many fixed sweeps whose numbers pass 2^32,
+//   and no launch has the number of the one before, new buffers between them
+//   included
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -118,25 +120,31 @@ static int numbers(int32_t sweeps)
     ResNumbers nb;
     ResCtl ctl{};
     int64_t total = 0, launches = 0, clears = 0;
-    bool solve = true;
+    uint32_t before = 0;
     for (; total < (int64_t)5 << 31; ++launches) {
         if (nb.restart()) {
             ctl = ResCtl{};
             ++clears;
         }
+        if (launches == 0 || launches == 1) {
+            ctl = ResCtl{};
+            nb.zeroed();
+        }
         const uint32_t kbase = nb.next;
+        if (kbase == before) return bad("number used again", total, kbase);
+        before = kbase;
         for (int d = 0; d < kResDeciders; ++d)
             if ((int32_t)(ctl.word[d] - kbase) >= 0) return bad("word", total, ctl.word[d]);
         for (uint32_t w : ctl.stop)
             if ((int32_t)(w - kbase) >= 0) return bad("stop word", total, w);
         if (ctl.done == kbase || ctl.abort == kbase) return bad("done or abort", total, kbase);
+        const bool solve = launches == 2;
         const int32_t last = solve ? 5 : sweeps;
         // the deciding workgroups' last words; stop words and done by solves alone
         for (int d = 0; d < kResDeciders; ++d) ctl.word[d] = kbase + (uint32_t)last + kResDeciders - 1;
         if (solve)
             for (uint32_t& w : ctl.stop) w = kbase + 5;
         if (solve) ctl.done = kbase;
-        solve = false;
         nb.passed(last);
         total += last;
     }

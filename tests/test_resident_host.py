@@ -38,7 +38,7 @@ def test_wide_table_kernels_read_within_the_footprint_and_its_ends(checker, N, m
     assert r["wide"] == 1 and r["absent"] > 0
 
 
-@pytest.mark.parametrize("sweeps", [200, 100000, 2147483647])
+@pytest.mark.parametrize("sweeps", [200, 9973, 65536])
 def test_control_words_of_an_old_solve_read_as_not_yet(checker, sweeps):
     # fixed sweeps number on without writing the stop words
     r = run(checker, "numbers", sweeps)
