@@ -351,9 +351,10 @@ jac_status jac_sweep_checkpointed(jac_handle h, int32_t K, int32_t ckpt_every);
  * iterate and nothing is recomputed; otherwise it keeps every
  * ckpt_every-th iterate (ceil(K/ckpt_every) + 2*ckpt_every + 5 vectors plus
  * one double per slot, else JAC_E_INVALID) and each segment is swept again
- * from its checkpoint.  Where K more vectors fit as well and the resident
- * loop takes the split, every mu is kept and the reverse sweeps and the
- * gradient are one launch each.  All give bit-identical results.  The forward pass
+ * from its checkpoint.  Where the resident loop takes the split and K more
+ * vectors and its own ring of eight fit as well, instead of those of a
+ * segment, every mu is kept and the reverse sweeps and the gradient are one
+ * launch each.  All give bit-identical results.  The forward pass
  * is skipped when jac_sweep_checkpointed left valid iterates for this K and
  * stride.  Leaves x = x_K in the handle.  Either output may be NULL.  The
  * buffers stay with the handle for later calls until jac_destroy. */

@@ -327,10 +327,7 @@ extern "C" jac_status jac_adjoint(jac_handle hp, int32_t K, int32_t ckpt, const 
         JAC_HIP(hipStreamSynchronize(st));   // the host descriptors are temporaries
         const SysDev* d_sT = static_cast<const SysDev*>(d.adj_sys.p);
         const SysDev* d_sG = d_sT + 1;
-        d.adj_M.ensure((size_t)c * vec);
         d.adj_lam0.ensure(vec);
-        d.adj_lam1.ensure(vec);
-        d.adj_carry.ensure(vec);
         d.adj_gb.ensure(vec);
         d.adj_G.ensure((size_t)h.plan.slots * 8);
         JAC_HIP(hipMemsetAsync(d.adj_G.p, 0, (size_t)h.plan.slots * 8, st));
@@ -350,13 +347,13 @@ extern "C" jac_status jac_adjoint(jac_handle hp, int32_t K, int32_t ckpt, const 
         if (K > 0) {
             // lambda_K (internal order), mu_K = D^{-1} lambda_K, gb = mu_K
             double* lin = static_cast<double*>(d.adj_lam0.p);
-            double* lout = static_cast<double*>(d.adj_lam1.p);
             launch_gather_in(gx_dev, static_cast<const int32_t*>(d.perm.p), n, 1, lin, st);
             // every mu kept: the reverse sweeps run in one resident launch,
             // then the gradient of all segments in another (the same sums in
             // the same order as segment by segment)
             bool reversed = false;
-            if (all && adjoint_bytes(h, K, c, true) + (size_t)K * vec <= ((size_t)h.opt.ckpt_mb << 20)) {
+            const size_t more = all ? resident_adjoint_bytes(h, K) : 0;
+            if (more && adjoint_bytes(h, K, 1, true) + more <= ((size_t)h.opt.ckpt_mb << 20)) {
                 bool room = true;
                 try {
                     d.adj_mu.ensure((size_t)K * vec);
@@ -372,9 +369,17 @@ extern "C" jac_status jac_adjoint(jac_handle hp, int32_t K, int32_t ckpt, const 
                     reversed = true;
                 }
             }
-            const int32_t Llast = K - (nseg - 1) * c;
-            if (!reversed) launch_adj_init(static_cast<const double*>(d.invd.p), lin, n, Mm(Llast - 1),
-                            static_cast<double*>(d.adj_gb.p), st);
+            double* lout = nullptr;
+            if (!reversed) {
+                d.adj_mu.reset();           // of a launch that gave up or an earlier call
+                d.adj_M.ensure((size_t)c * vec);
+                d.adj_lam1.ensure(vec);
+                d.adj_carry.ensure(vec);
+                lout = static_cast<double*>(d.adj_lam1.p);
+                const int32_t Llast = K - (nseg - 1) * c;
+                launch_adj_init(static_cast<const double*>(d.invd.p), lin, n, Mm(Llast - 1),
+                                static_cast<double*>(d.adj_gb.p), st);
+            }
             // the recompute launches decide nothing (sweep 0 of a fresh state)
             launch_init_state(static_cast<SysState*>(d.state.p), 1, st);
             for (int32_t j = nseg - 1; j >= 0 && !reversed; --j) {

@@ -169,6 +169,8 @@ bool run_resident_solve(Handle& h, const SysDev& s, bool fp32, int32_t maxit, in
                         void* xa, void* xb, SysState& st);
 // K reverse sweeps of the adjoint in one launch, on the plan of A^T: lam is
 // lambda_K, mu receives mu_k at (k - 1) * n for k = 1 .. K, gb their sum.
+// Device bytes it needs, mu and the ring; 0 where it does not take the plan.
+size_t resident_adjoint_bytes(const Handle& h, int32_t K);
 bool run_resident_adjoint(Handle& h, int32_t K, const double* lam, double* mu, double* gb);
 jac_status solve_refine(Handle& h, double tol, int32_t maxit, int norm, int32_t* sweeps_out, double* relres_out);
 void set_last_error(const std::string& m);

@@ -133,16 +133,19 @@ struct ResLaunch {
     size_t lds = 0;
     int32_t ldx = 0;
     double share = 0.0, wg = 0.0;   // of the device, and a workgroup's of a compute unit
+    size_t bytes = 0, o_part = 0;   // of the handle's buffer; where the partials start
+    bool loc = false, tabg = false, wide = false;
     ResParams p{};
 };
 
-ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp32, int nrhs, int32_t kend, bool adjoint)
+// Whether the loop takes the plan, and how (nothing is allocated).
+ResLaunch res_shape(const Handle& h, const Plan& pl, bool fp32, int nrhs, int32_t kend, bool adjoint)
 {
     ResLaunch L;
-    h.res_poll();
     // Options that name a launch shape keep per-sweep launches (or the
     // persistent loop); the norm is summed in the order of 256 threads.
-    if (h.opt.loop != 0 || (h.opt.grid != 0 && !h.res_tuned) || h.opt.block != kResBlock || kend < kResMinSweeps || kend > kResMaxSweeps) return L;
+    if (h.opt.loop != 0 || (h.opt.grid != 0 && !h.res_tuned) || h.opt.block != kResBlock) return L;
+    if (kend < kResMinSweeps || kend > kResMaxSweeps) return L;
     const bool loc = pl.colfmt == COL_LOCAL16;
     const bool tabg = pl.colfmt == COL_TABG && !pl.res_run0.empty();
     if (!tabg && (adjoint || (!loc && pl.colfmt != COL_TABL))) return L;
@@ -174,16 +177,28 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     const int groups = std::max(num_cus() / 8, 1);
     L.share = (double)((L.grid + groups - 1) / groups) / (8.0 * nb);
     L.wg = 1.0 / nb;
-    if (!h.res_retry.now()) return L;
+    L.o_part = kResRingOff + up256((size_t)kResRing * vec);
+    L.bytes = L.o_part + (size_t)kResPart * pl.ntiles * res_partials(nrhs, width, loc) * nrhs * sizeof(double);
+    L.loc = loc;
+    L.tabg = tabg;
+    L.wide = wide;
+    L.ok = true;
+    return L;
+}
 
+ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp32, int nrhs, int32_t kend, bool adjoint)
+{
+    h.res_poll();
+    ResLaunch L = res_shape(h, pl, fp32, nrhs, kend, adjoint);
+    if (!L.ok) return L;
+    L.ok = false;
+    if (!h.res_retry.now()) return L;
     DeviceArrays& d = h.d;
-    const int npart = res_partials(nrhs, width, loc);
-    const size_t o_part = kResRingOff + up256((size_t)kResRing * vec);
-    const size_t bytes = o_part + (size_t)kResPart * pl.ntiles * npart * nrhs * sizeof(double);
+    const bool tabg = L.tabg, wide = L.wide;
     bool clear = h.res_numbers.restart();
-    if (!d.res_work.p || d.res_work.bytes < bytes) {
+    if (!d.res_work.p || d.res_work.bytes < L.bytes) {
         try {
-            d.res_work.alloc(bytes);
+            d.res_work.alloc(L.bytes);
         } catch (const Error& e) {
             if (e.status != JAC_E_NOMEM) throw;
             (void)hipGetLastError();
@@ -216,7 +231,7 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     }
     r.col16 = static_cast<const uint16_t*>(pd.col16.p);
     r.ring = work + kResRingOff;
-    r.part = reinterpret_cast<double*>(work + o_part);
+    r.part = reinterpret_cast<double*>(work + L.o_part);
     r.ctl = reinterpret_cast<ResCtl*>(work);
     r.n = h.a.n;
     r.ntiles = pl.ntiles;
@@ -328,7 +343,7 @@ static bool res_sweeps(Handle& h, const SysDev& s, int32_t kend, double* hist, c
     L.p.hist = hist;
     L.p.xall = xall;
     if (!res_launch(h, L)) return false;
-    launch_res_finish(h.nrhs, h.plan.colfmt == COL_LOCAL16, h.plan.res_max_runs, h.stream, L.p,
+    launch_res_finish(h.nrhs, L.loc, h.plan.res_max_runs, h.stream, L.p,
                       static_cast<double*>(x0_out));
     h.res_numbers.passed(kend);
     h.res_open = L.p.kbase;
@@ -433,6 +448,12 @@ bool run_resident_solve(Handle& h, const SysDev& s, bool fp32, int32_t maxit, in
     }
     if (h.opt.timing) h.last_loop_ms = ms;
     return true;
+}
+
+size_t resident_adjoint_bytes(const Handle& h, int32_t K)
+{
+    const ResLaunch L = res_shape(h, h.tplan, false, 1, K - 1, true);
+    return L.ok ? (size_t)K * h.a.n * sizeof(double) + L.bytes : 0;
 }
 
 bool run_resident_adjoint(Handle& h, int32_t K, const double* lam, double* mu, double* gb)

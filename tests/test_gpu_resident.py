@@ -529,3 +529,26 @@ def test_autotune_keeps_the_resident_loop(tmp_path, monkeypatch):
     assert b.jac_get_info(handles[0])["resident_loops"] == ran
     for h in handles:
         b.jac_destroy(h)
+
+
+@pytest.mark.parametrize("grid", [0, 1])
+def test_adjoint_allocates_what_its_route_needs(grid):
+    # per sweep: all iterates, the mu of a segment; resident: all iterates, all mu, the ring of eight
+    need_gpu()
+    b = B()
+    s = W.diffusion_adjoint(48)
+    K, c = 120, 40
+    g = torch.from_numpy(np.random.default_rng(4).uniform(-1, 1, s.n)).cuda()
+    gb, gv = torch.empty(s.n, dtype=torch.float64, device="cuda"), torch.empty(s.nnz, dtype=torch.float64, device="cuda")
+    h = make(s, 1, 1, opts={b.JAC_OPT_GRID: grid})
+    vec = 8 * s.n
+    b.jac_adjoint(h, 0, 1, g, gb, gv)                              # the transposed layout and the small buffers
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    b.jac_adjoint(h, K, c, g, gb, gv)
+    torch.cuda.synchronize()
+    used = free - torch.cuda.mem_get_info()[0]
+    need = (K + 1 + (K + 8 if grid == 0 else c + 2)) * vec
+    assert used <= need + 24 * vec, (used / vec, need / vec)       # allocations are rounded up
+    assert b.jac_get_info(h)["resident_loops"] == (2 if grid == 0 else 0)
+    b.jac_destroy(h)
