@@ -193,7 +193,11 @@ Plan make_plan(const Csr& a, const std::vector<int32_t>& cuts_in, const PlanPara
     // shifts the LDS positions behind it, so that a slice reaches its columns
     // through more shifts, each a padded slot for all its rows (80^3 27-point
     // matrix with a tenth of its edges dropped: 30 slots in the widest slices,
-    // 27 with the holes staged).
+    // 27 with the holes staged).  The other loops lose nothing, at sizes far
+    // beyond the resident loop's too (sweeps without and with the holes: 72^3
+    // 17.9 and 17.7 us, 96^3 34.6 and 34.4, 112^3 65.1 and 65.1, 128^3 95.6 and
+    // 94.5; FP32 refinement at 96^3 8.44 and 8.37 ms), but the split takes a
+    // sixth to a fifth longer (128^3 3.2 and 3.9 s).
     if (prm.staged && prm.tables && tab_bytes < ell_bytes && max_tab_width > kResWidth &&
         max_tab_width <= kResWidth + 13 && prm.fill_gap > 0) {
         const std::vector<Footprint> plain = fps;

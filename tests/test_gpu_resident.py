@@ -552,3 +552,76 @@ def test_adjoint_allocates_what_its_route_needs(grid):
     assert used <= need + 24 * vec, (used / vec, need / vec)       # allocations are rounded up
     assert b.jac_get_info(h)["resident_loops"] == (2 if grid == 0 else 0)
     b.jac_destroy(h)
+
+
+@pytest.mark.parametrize("r", [1, 2, 4])
+@pytest.mark.parametrize("half", [2, 4, 6, 9, 13])
+@pytest.mark.parametrize("tables", [0, 1])
+def test_every_kernel_of_the_loop(half, r, tables):
+    # 5, 9, 13, 19 and 27 slots, from a shift table and as explicit columns,
+    # FP64 and FP32: each runs, and gives the bits of per-sweep launches
+    need_gpu()
+    b = B()
+    s = with_rhs(banded(1700, half), r)
+    x0 = np.random.default_rng(5).uniform(-1, 1, (r, s.n))
+    out = []
+    for g in (1, 0):
+        h = make(s, 2, 3, opts={b.JAC_OPT_GRID: g, b.JAC_OPT_SHIFT_TABLES: tables})
+        b.jac_partition(h, 2, 3, None)
+        assert b.jac_get_info(h)["col_format"] == (4 if tables else 2)
+        set_x(h, x0)
+        res = [sweep(h, 20, r), get_x(h, s.n, r)]
+        for prec in (b.JAC_FP64, b.JAC_FP32_REFINE):
+            b.jac_set_x(h, None)
+            st, sw, rr = b.jac_solve(h, 1e-10, 5000, b.JAC_NORM_L2_REL, prec)
+            assert st == b.JAC_OK
+            res += [sw, rr, get_x(h, s.n, r)]
+        ran = b.jac_get_info(h)["resident_loops"]
+        assert ran == 0 if g else ran >= 3, ran
+        out.append(res)
+        b.jac_destroy(h)
+    for k, (u, v) in enumerate(zip(*out)):
+        assert np.array_equal(u, v), k
+
+
+@pytest.mark.parametrize("half", [3, 4, 6, 9, 13])
+def test_every_reverse_kernel_of_the_loop(half):
+    need_gpu()
+    b = B()
+    s = banded(1700, half)
+    g = np.random.default_rng(4).uniform(-1, 1, s.n)
+    out = []
+    for grid in (1, 0):
+        h = make(s, 1, 3, opts={b.JAC_OPT_GRID: grid})
+        gb = torch.empty(s.n, dtype=torch.float64, device="cuda")
+        gv = torch.empty(s.nnz, dtype=torch.float64, device="cuda")
+        b.jac_adjoint(h, 25, 6, torch.from_numpy(g).cuda(), gb, gv)
+        assert b.jac_get_info(h)["resident_loops"] == (0 if grid else 2)       # forward and reverse
+        out.append((gb.cpu().numpy(), gv.cpu().numpy(), get_x(h, s.n)))
+        b.jac_destroy(h)
+    for k, (u, v) in enumerate(zip(*out)):
+        assert np.array_equal(u, v), k
+
+
+def test_loops_of_threads_are_resident():
+    need_gpu()
+    b = B()
+    s = W.laplace7(18, workload=1)
+    ran, errors = [0] * 4, []
+
+    def work(q):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                h = make(s, 2, 3)
+                for _ in range(5):
+                    b.jac_set_x(h, None)
+                    b.jac_solve(h, 1e-8, 5000)
+                ran[q] = b.jac_get_info(h)["resident_loops"]
+                b.jac_destroy(h)
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    ts = [threading.Thread(target=work, args=(q,)) for q in range(4)]
+    [t.start() for t in ts]
+    [t.join(60) for t in ts]
+    assert not errors and ran == [5] * 4

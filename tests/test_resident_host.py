@@ -43,3 +43,13 @@ def test_control_words_of_an_old_solve_read_as_not_yet(checker, sweeps):
     # fixed sweeps number on without writing the stop words
     r = run(checker, "numbers", sweeps)
     assert r["clears"] >= 2
+
+
+@pytest.mark.parametrize("N,points,mode,P,fmt", [(24, 7, 1, 8, 3), (17, 7, 2, 5, 4), (24, 7, 3, 8, 2), (15, 27, 1, 4, 3),
+                                                 (22, 27, 2, 4, 4), (15, 27, 3, 4, 2)])
+def test_footprints_decode_to_the_columns_of_the_other_loops(checker, N, points, mode, P, fmt):
+    r = run(checker, "layout", N, points, mode, P)
+    assert r["fmt"] == fmt and r["width"] <= 27
+    # columns no entry of the tile has: what tables reach beyond their rows' entries, and the holes of the
+    # 22^3 footprints, staged so that its widest slices take the loop's 27 slots
+    assert (r["holes"] > 0) == (fmt == 3 or N == 22), r
