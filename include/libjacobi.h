@@ -89,7 +89,8 @@ typedef enum {
     JAC_OPT_LOOP = 4,        /* 0 = (default) where the split's tiles all fit the
                                 device at once, the tile, block and grid
                                 options leave it open and a call has eight
-                                sweeps or more: every sweep in one resident
+                                sweeps or more (sixteen on larger systems with
+                                few entries a row): every sweep in one resident
                                 launch, beside those of other streams where the
                                 device holds both and after them else; one
                                 launch per sweep otherwise, also while another
@@ -164,7 +165,10 @@ typedef struct {
     int64_t halo_entries;        /* sum of the receive lists                        */
     int64_t staged_entries;      /* sum over tiles of staged x entries             */
     int64_t alg_bytes_per_sweep; /* 12 nnz + 4 (n+1) + 8 n + 24 n nrhs (CSR model)   */
-    int64_t dev_bytes_per_sweep; /* bytes the kernel actually streams per sweep     */
+    int64_t dev_bytes_per_sweep; /* bytes the kernel of a per-sweep launch streams (a
+                                    resident loop reads the matrix once for all its
+                                    sweeps: only b, x and the entries that tiles
+                                    exchange go to and from memory at each)         */
     int32_t loop_grid;           /* workgroups of the last sweep loop (resident
                                     loop: one per tile and four that decide)        */
     int32_t block;               /* threads per workgroup                           */

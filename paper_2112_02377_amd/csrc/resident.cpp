@@ -14,10 +14,16 @@ namespace jac {
 
 namespace {
 
-// A loop this short costs less as per-sweep launches: a resident launch
-// takes about 20 us from queue to queue, a per-sweep launch of a small
-// system 5.4 us against 1.5-2.5 us for a resident sweep.
-constexpr int32_t kResMinSweeps = 8;
+// A shorter loop costs less as per-sweep launches: a resident launch clears
+// its ring and loads its matrix first.  Eight sweeps, launched per sweep and
+// resident: 16^3 73 and 36 us, 64^3 87 and 79, 56^3 of 27-point rows 138 and
+// 89.  With rows of a 7-point matrix, beyond some 640 tiles or 4 MB of x the
+// start takes longer than eight sweeps gain: 72^3 97 and 108 us at eight, 152
+// and 138 at sixteen; 80^3 118 and 141, 196 and 179; 84^3 129 and 169, 216 and
+// 216; 64^3 of four columns 137 and 148, 229 and 217 (48^3 of four: 100 and 73).
+constexpr int32_t kResMinSweeps = 8, kResMinSweepsLarge = 16;
+constexpr int32_t kResLargeTiles = 640;
+constexpr size_t kResLargeBytes = 4000000;
 // Sweeps of one launch at most: it occupies its compute units until it ends
 // (65536 sweeps are 0.15 to 0.35 s), where other streams' work got its turn
 // between per-sweep launches.  Longer loops are several launches; one more
@@ -159,6 +165,7 @@ ResLaunch res_shape(const Handle& h, const Plan& pl, bool fp32, int nrhs, int32_
     if (pl.res_max_halo + ends > res_halo(width) * kResBlock) return L;
     const size_t ts = fp32 ? 4 : 8, vec = (size_t)h.a.n * nrhs * ts;
     if (vec >= ((size_t)1 << 32)) return L;              // 32-bit byte offsets into a ring slot
+    if (width <= 14 && (pl.ntiles > kResLargeTiles || vec > kResLargeBytes) && kend < kResMinSweepsLarge) return L;
     L.fn = adjoint ? res_adjoint_kernel(width, per_wave) : res_kernel(fp32, nrhs, width, per_wave, loc);
     if (!L.fn) return L;
     L.ldx = pl.res_max_fp + (wide ? kResEnds : 1);       // and a zero for slots past a slice's width

@@ -625,3 +625,23 @@ def test_loops_of_threads_are_resident():
     [t.start() for t in ts]
     [t.join(60) for t in ts]
     assert not errors and ran == [5] * 4
+
+
+@pytest.mark.parametrize("edge,r,least", [(48, 1, 8), (64, 1, 8), (72, 1, 16), (80, 1, 16), (64, 4, 16), (48, 4, 8)])
+def test_short_loops_of_large_systems_are_launched_per_sweep(edge, r, least):
+    # where filling the ring and loading the matrix take longer than the sweeps gain
+    need_gpu()
+    b = B()
+    s = with_rhs(W.laplace7(edge, workload=1), r)
+    out = []
+    for g in (1, 0):
+        h = make(s, 1, 4, opts={b.JAC_OPT_GRID: g})
+        res = []
+        for k, loops in ((least - 1, 0), (least, 1 - g)):
+            ran = b.jac_get_info(h)["resident_loops"]
+            res += [sweep(h, k, r)]
+            assert b.jac_get_info(h)["resident_loops"] == ran + loops
+        out.append(res + [get_x(h, s.n, r)])
+        b.jac_destroy(h)
+    for u, v in zip(*out):
+        assert np.array_equal(u, v)
