@@ -199,6 +199,12 @@ ResLaunch res_prepare(Handle& h, const Plan& pl, const DeviceArrays& pd, bool fp
     ResLaunch L = res_shape(h, pl, fp32, nrhs, kend, adjoint);
     if (!L.ok) return L;
     L.ok = false;
+    // A captured launch would carry the numbers of this one at every replay.
+    // (The per-sweep loop cannot be captured either: it waits for its stream.)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h.stream, &capture) != hipSuccess) (void)hipGetLastError();
+    else if (capture != hipStreamCaptureStatusNone)
+        fail(JAC_E_HIP, "the stream is being captured; of the sweep loops only jac_sweep_noalloc can be");
     if (!h.res_retry.now()) return L;
     DeviceArrays& d = h.d;
     const bool tabg = L.tabg, wide = L.wide;

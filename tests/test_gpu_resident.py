@@ -645,3 +645,33 @@ def test_short_loops_of_large_systems_are_launched_per_sweep(edge, r, least):
         b.jac_destroy(h)
     for u, v in zip(*out):
         assert np.array_equal(u, v)
+
+
+def test_sweeps_are_not_captured():
+    # a resident launch carries numbers that must not come again, so a graph
+    # of it would be wrong from its second replay on: a capture is refused,
+    # as it is by the per-sweep loop, and the handle goes on
+    import ctypes
+    need_gpu()
+    b = B()
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
+    hip = ctypes.CDLL(path)
+    s = W.laplace7(16, workload=1)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        h = make(s, 1, 2)
+        b.jac_sweep(h, 20, None)
+        st.synchronize()
+        want = get_x(h, s.n)
+        graph = ctypes.c_void_p()
+        assert hip.hipStreamBeginCapture(ctypes.c_void_p(st.cuda_stream), 2) == 0      # relaxed
+        with pytest.raises(b.JacError) as e:
+            b.jac_sweep(h, 20, None)
+        assert hip.hipStreamEndCapture(ctypes.c_void_p(st.cuda_stream), ctypes.byref(graph)) == 0
+        assert e.value.status == b.JAC_E_HIP and hip.hipGraphDestroy(graph) == 0
+        torch.cuda.synchronize()
+        assert np.array_equal(get_x(h, s.n), want)
+        b.jac_set_x(h, None)
+        b.jac_sweep(h, 20, None)
+        assert np.array_equal(get_x(h, s.n), want)
+        b.jac_destroy(h)
