@@ -68,7 +68,7 @@ def parse():
     return ap.parse_args()
 
 
-KERNEL_SOURCES = ("kernels.hip", "kernels.h", "launch.h")
+KERNEL_SOURCES = ("kernels.hip", "device.h", "kernels.h", "launch.h")
 
 
 def log(msg):
@@ -228,7 +228,9 @@ def secondary(B, W, torch, stream, with_oracle=True, persistent=True, legs=SECON
     relaxation against the synchronous solve, and the control configurations
     (20^3 solves, 128^3 with 4x4x4 subdomains).  `legs` selects among them.
     Times are HIP-event times on the handles' stream."""
-    out = {}
+    out = {"rates": "GBps fields are model bytes per sweep times sweeps over time; a resident loop reads the matrix "
+                    "once, so on systems it takes they are a rate of work, not of memory traffic, and may pass the "
+                    "memory's peak"}
     if "refine" in legs:
         log("secondary: FP32 refinement")
         out["fp32_refine"] = refine_leg(B, W, torch, stream, with_oracle)

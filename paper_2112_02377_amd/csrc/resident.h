@@ -168,7 +168,7 @@ struct ResParams {
     int32_t kend, solve, norm_inf;
 };
 
-// Kernel for slots per row (7, 14 or 28) and slices per wave (2 or 4), or null when there is none.
+// Kernel for up to 7, 14 or 27 slots per row and up to two slices per wave, or null when there is none.
 void* res_kernel(bool fp32, int nrhs, int width, int slices, bool explicit_cols);
 // Reverse sweeps of the adjoint (FP64, one column, shift table).
 void* res_adjoint_kernel(int width, int slices);

@@ -9,9 +9,11 @@
 // What bounds a sweep is then the trip of a value from one workgroup to
 // another through device-coherent memory (about 1.0-1.5 us measured with up
 // to 256 workgroups, 1.8 us with 512), where a launch per sweep costs
-// 5.4 us at 20^3 and 6.8 us at 64^3.  Whole solves, a launch per sweep against
-// this loop: 20^3 Laplacian 7.10 and 2.95 ms, 33^3 and 65^3 Q1 cubes 6.54 and
-// 2.40, 39.2 and 12.1 ms, 56^3 27-point matrix 4.87 and 1.67 ms.
+// 4.8 us at 20^3 and 5.8 us at 64^3.  A sweep of this loop takes 1.9 us in
+// fixed sweeps and 2.2 in solves at 20^3, 3.2 at 64^3, and with 27 slots a
+// row 3.1 at 33^3, 4.4 at 56^3, 5.4 at 65^3.  Whole solves, a launch per sweep
+// against this loop: 20^3 Laplacian 7.10 and 2.81 ms, 33^3 and 65^3 Q1 cubes
+// 6.54 and 2.39, 39.2 and 12.1 ms, 56^3 27-point matrix 4.87 and 1.67 ms.
 //
 // Exchange without fences or barriers across workgroups: x_k is published in
 // slot k mod 8 of a ring with relaxed device-scope stores, one per value.  A
@@ -765,8 +767,8 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
             // delay: another tile's store needs some 0.4 us to be seen, and a
             // try that comes before it costs its whole trip and leaves the
             // line in this XCD's L2, which the store then has to take back
-            // (20^3 2.13 us a sweep without the pause, 1.91 with; 80^3 4.86
-            // and 4.4).
+            // (fixed sweeps without the pause and with it: 20^3 1.86 and 1.91
+            // us, 33^3 2.08 and 1.94, 64^3 3.23 and 3.14, 80^3 5.13 and 4.85).
             if (tid == CT) {
                 const int32_t need = k + 4 - kResRing;
                 if (need >= 0 && word < need) {
@@ -858,7 +860,9 @@ __device__ void res_tile(const ResParams& P, int32_t tile, char* smem, int32_t l
 }
 
 // Waves per SIMD asked of the compiler: what the registers held across a
-// sweep leave room for.
+// sweep leave room for, some at the price of a spill (14 registers in the
+// FP64 four-column 7-slot kernels, 4 in the 27-slot adjoint, 2 and 1 in the
+// FP32 27-slot ones, 1 in the FP64 27-slot table kernel).
 template <typename T>
 constexpr int res_waves(int nrhs, int w, bool loc, bool adj)
 {
