@@ -340,9 +340,20 @@ def test_a_launch_that_gives_up_is_repeated_per_sweep(name):
         b.jac_destroy(h)
 
 
+TICKS = []
+
+
 def busy_stream(ms):
     """Puts about `ms` of device work on the current stream and returns an event behind it."""
-    torch.cuda._sleep(int(ms * 1e-3 * 1.0e8))                     # ticks of the device's 100 MHz clock
+    if not TICKS:                                                 # of the clock that _sleep counts, per ms
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        for k in range(2):
+            e[0].record()
+            torch.cuda._sleep(2000000)
+            e[1].record()
+            torch.cuda.synchronize()
+        TICKS.append(2000000 / e[0].elapsed_time(e[1]))
+    torch.cuda._sleep(int(ms * TICKS[0]))
     e = torch.cuda.Event()
     e.record()
     return e
