@@ -67,9 +67,20 @@ struct Loop {
     uint32_t kbase;                 // its last launch
     double share, wg;
 };
+// A call that waits for room, in the order in which they came.
+using Clock = std::chrono::steady_clock;
+struct Waiter {
+    const Handle* h;
+    Clock::time_point since;
+};
 constexpr int kMaxDevices = 64;
 std::mutex g_loops_mutex;
 std::vector<Loop> g_loops[kMaxDevices];
+std::vector<Waiter> g_waiters[kMaxDevices];
+// Nobody enters past a call that has waited this long: without that a thread
+// with one loop after the other kept another out for 100 ms (two threads with
+// 4 ms solves at 64^3); with it the longest call takes 8.5.
+constexpr auto kPatience = std::chrono::milliseconds(2);
 
 // Whether a launch of that share may go on the handle's stream.  Waits for
 // room, but only behind launches that are running: one behind other work on
@@ -81,10 +92,15 @@ Entry loops_enter(const Handle& h, double share, double wg)
 {
     if (h.device < 0 || h.device >= kMaxDevices) return Entry::no;
     int held = 0;
+    std::vector<Waiter>& waiters = g_waiters[h.device];
+    auto mine = [&](const Waiter& w) { return w.h == &h; };
+    auto leave = [&]() { waiters.erase(std::remove_if(waiters.begin(), waiters.end(), mine), waiters.end()); };
     for (int tries = 0; tries < 20000; ++tries) {
         {
             std::lock_guard<std::mutex> lock(g_loops_mutex);
             std::vector<Loop>& v = g_loops[h.device];
+            const Clock::time_point now = Clock::now();
+            const bool after = !waiters.empty() && waiters.front().h != &h && now - waiters.front().since > kPatience;
             Loop me{&h, h.stream, static_cast<const ResSeen*>(h.d.res_seen.p), h.res_numbers.next, share, wg};
             double total = 0.0, most = wg;
             bool running = true;
@@ -102,7 +118,9 @@ Entry loops_enter(const Handle& h, double share, double wg)
                     ++q;
                 }
             }
-            if (total == 0.0 || total + me.share + std::max(most, me.wg) <= 1.0) {
+            const bool fits = total == 0.0 || total + me.share + std::max(most, me.wg) <= 1.0;
+            if (fits && !after) {
+                leave();
                 v.erase(std::remove_if(v.begin(), v.end(),
                                        [&](const Loop& q) {
                                            return q.holder == &h ||
@@ -113,10 +131,16 @@ Entry loops_enter(const Handle& h, double share, double wg)
                 return total == 0.0 ? Entry::alone : Entry::beside;
             }
             held = running ? 0 : held + 1;       // a launch takes some time to start, too
-            if (held > 10) return Entry::no;
+            if (held > 10) {
+                leave();
+                return Entry::no;
+            }
+            if (std::none_of(waiters.begin(), waiters.end(), mine)) waiters.push_back({&h, now});
         }
         std::this_thread::sleep_for(std::chrono::microseconds(20));
     }
+    std::lock_guard<std::mutex> lock(g_loops_mutex);
+    leave();
     return Entry::no;
 }
 

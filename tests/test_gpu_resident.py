@@ -686,3 +686,39 @@ def test_sweeps_are_not_captured():
         b.jac_sweep(h, 20, None)
         assert np.array_equal(get_x(h, s.n), want)
         b.jac_destroy(h)
+
+
+def test_no_thread_is_kept_out_by_the_loops_of_another():
+    # two threads, one solve after the other, of which only one fits the
+    # device: each gets its turns (a call is two solves long then; without a
+    # queue the longest took more than ten)
+    need_gpu()
+    import time
+    b = B()
+    s = W.laplace7(64, workload=1)
+    took, errors = [[], []], []
+    start = threading.Barrier(2)
+
+    def work(q):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                h = make(s, 1, 4)
+                b.jac_solve(h, 1e-3, 100000)
+                start.wait(30)
+                end = time.perf_counter() + 1.5
+                while time.perf_counter() < end:
+                    t = time.perf_counter()
+                    b.jac_set_x(h, None)
+                    b.jac_solve(h, 1e-3, 100000)
+                    took[q].append(time.perf_counter() - t)
+                b.jac_destroy(h)
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    ts = [threading.Thread(target=work, args=(q,)) for q in range(2)]
+    [t.start() for t in ts]
+    [t.join(60) for t in ts]
+    assert not errors
+    alone = min(took[0] + took[1])
+    for t in took:
+        assert np.percentile(t, 98) < 8 * alone and sum(t) < 3.0, (alone, np.percentile(t, 98), max(t))
